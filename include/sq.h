@@ -149,9 +149,8 @@ int sq_init(void);
 size_t sq_act_bytes(const sq_params *p, size_t *d_lo, size_t *hi_val, size_t *mask, size_t *scale);
 
 /* Bytes of device workspace sq_gemm needs when a->hi_dense is NULL (dynamic: the image of the
- * high part, M*K bytes; static: none -> returns 16 so that a valid pointer can always be passed, except for
- * M <= 32 with K % 128 == 0, where a workspace of M*K bytes lets sq_gemm run the weight-streaming decode kernel
- * on the dense low part and an image of the high part; without it the generic tile runs). */
+ * high part, M*K bytes; static: none -> returns 16, or M*K for M <= 32 with K % 128 == 0, so that a valid pointer can
+ * always be passed; it is not used). */
 size_t sq_gemm_workspace_bytes(const sq_params *p);
 
 /* Bytes of device workspace sq_linear needs: the encoded activations in the form sq_gemm multiplies
@@ -207,10 +206,12 @@ int sq_encode(const sq_params *p, const uint16_t *x_bf16, int64_t ldx, const uin
 int sq_gemm(const sq_params *p, const sq_act *a, const sq_weight *w, void *y, int64_t ldy,
             int32_t *acc_lo_dbg, int32_t *acc_hi_dbg, void *workspace, size_t workspace_bytes, void *stream);
 
-/* Which of its kernels sq_gemm / sq_linear run for these parameters (static storage, never NULL):
- * "tile256x256" (SQ_DYNAMIC_TIED on shapes with at least 512 tiles of 256 x 256), "tile128x256" (workgroup tile of 128 tokens x 256 output channels; shapes with more than 128 such tiles),
- * "tile128x128" (fewer tiles), "tile64x64" (M <= 64), "tile64x128" (33 <= M <= 64 and N >= 25473), "stream32" (dynamic mode, M <= 32, K % 128 == 0: the
- * weight-streaming decode kernel), or "invalid".  Informational: tests use it to state which kernel a case covers. */
+/* The size class of these parameters (static storage, never NULL): "tile256x256" (SQ_DYNAMIC_TIED on shapes with at
+ * least 512 tiles of 256 tokens x 256 output channels), "tile128x256" (more than 128 tiles of that size),
+ * "tile128x128" (fewer), "tile64x64" (M <= 64), "tile64x128" (33 <= M <= 64 and N >= 25473), "stream32" (dynamic mode,
+ * M <= 32, K % 128 == 0), or "invalid".  Informational.  The classes name the largest tile a shape of theirs is run
+ * with; inside a class the kernel is chosen by how many workgroups each tile gives (up to 32 tokens, and up to 64 on
+ * layers of at most 8192 channels: the few-token kernel, whose waves share K). */
 const char *sq_gemm_variant(const sq_params *p);
 
 /* sq_encode into the workspace followed by sq_gemm: Y = SQ(X) . W^T, everything on `stream`.

@@ -92,8 +92,13 @@ struct GemmArgs {
   int32_t* acc_hi_dbg;
 };
 int launch_gemm(const GemmArgs& g, hipStream_t st);
-// Name of the kernel variant launch_gemm picks for a shape ("tile256x256", "tile128x256", "tile128x128",
-// "tile64x64", "stream32").  dynamic: two products in one loop; single: one product (tied scales, plain W4A8).
+// Few tokens (sq_gemm_few.hip): which shapes, one-time initialisation, launcher.  mode: 0 dynamic (low + zero-padded
+// high), 1 static (low, then compact high), 2 one INT8 operand.
+bool gemm_few_supports(int M, int N);
+int init_gemm_few_kernels();
+int launch_gemm_few(const GemmArgs& g, int mode, hipStream_t st);
+// Name of a shape's size class ("tile256x256", "tile128x256", "tile128x128", "tile64x128", "tile64x64", "stream32").
+// dynamic: two products in one loop; single: one product (tied scales, plain W4A8).
 const char* gemm_variant_name(int M, int N, int K, bool dynamic, bool single);
 
 }  // namespace sq

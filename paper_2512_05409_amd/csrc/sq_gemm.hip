@@ -14,33 +14,30 @@
 // [evens of dword 2s | odds of dword 2s | evens of dword 2s+1 | odds of dword 2s+1].  The INT8
 // image of the high part is stored in exactly that byte order (see sq_act::hi_dense).
 //
-// Work split: a workgroup of 4 waves computes 128 tokens x 256 output channels; a wave computes
-// 64 tokens x 128 channels for BOTH products (2 x 2x4 tiles of 32x32, 256 accumulator registers).
+// Work split (the large tile): a workgroup of 4 waves computes 128 tokens x 256 output channels; a wave computes
+// 64 tokens x 128 channels for BOTH products (2 x 2x4 tiles of 32x32, 256 accumulator registers).  Smaller tiles, of
+// which a shape has at most a round, run two such groups of four waves per workgroup, each on every other K step.
 // A K step of 128 channels is copied into one of three LDS stages by LDS-direct loads, two steps
 // ahead of its use.  LDS rows are row-major with the 16-byte chunk index XOR-swizzled by the row,
 // which keeps the operand reads (32 consecutive rows per half wave) free of bank conflicts.
-#include "sq_device.h"
+#include "sq_gemm_common.h"
 
 namespace sq {
 namespace {
 
-typedef unsigned int v4u __attribute__((ext_vector_type(4)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
+using namespace gemm;
 
 constexpr int KS = 128;  // channels per K step
-#ifndef SQ_HUGE_MIN_TILES
-#define SQ_HUGE_MIN_TILES 512
-#endif
-constexpr int kHugeMinTiles = SQ_HUGE_MIN_TILES;
-  // 256x256 tiles a single-product shape needs to use them
+constexpr int kHugeMinTiles = 512;  // 256x256 tiles a single-product shape needs to use them
 constexpr int NT = 256;  // threads per workgroup
 
 // WITH_LO = false: a tile for loops without a packed low operand (the single-product modes), whose stage
 // holds no room for one; that is what lets 256 tokens x 256 channels fit three stages into LDS.
 // NS: LDS stages of the K loop.  The copy of step kt + NS - 1 is enqueued while step kt is multiplied, so a copy
 // has NS - 2 whole K steps to land before anything waits for it.
-template <int BM_, int BN_, bool WITH_LO = true, int NS_ = 3>
+template <int BM_, int BN_, bool WITH_LO = true, int NS_ = 3, int S_ = 1>
 struct Tile {
+  static constexpr int S = S_;                // K groups of four waves; group s takes the K steps s, s + S, ...
   static constexpr int NS = NS_;
   static constexpr int BM = BM_;              // tokens per workgroup
   static constexpr int BN = BN_;              // output channels per workgroup
@@ -52,18 +49,11 @@ struct Tile {
   static constexpr int A_HI = WITH_LO ? BM * 64 : 0;  // [BM][128 B]  INT8
   static constexpr int B_OFF = A_HI + BM * 128;  // [BN][64 B] packed INT4
   static constexpr int STAGE = B_OFF + BN * 64;
-  static constexpr int LDS_BYTES = NS * STAGE;
+  static constexpr int LDS_BYTES = S * NS * STAGE;
+  static constexpr int THREADS = NT * S;
   static_assert(NS >= 3 && LDS_BYTES <= 160 * 1024, "stages must fit in the 160 KB of LDS");
+  static_assert((S - 1) * BM * BN * 8 <= LDS_BYTES, "the other groups' partial sums must fit, too");
 };
-
-// Byte offset of 16-byte chunk c of a row inside an operand tile.
-__device__ __forceinline__ int off4(int row, int c) { return (row << 6) + (((c ^ (row >> 2)) & 3) << 4); }   // 4 chunks / row
-__device__ __forceinline__ int off8(int row, int c) { return (row << 7) + (((c ^ (row >> 1)) & 7) << 4); }   // 8 chunks / row
-
-// 16 zero bytes in device memory: the source of operand chunks that lie past the end of K.
-__device__ __attribute__((aligned(16))) const unsigned int kZeroChunk[4] = {0u, 0u, 0u, 0u};
-
-typedef __attribute__((address_space(3))) void* lds_ptr_t;
 
 // s_waitcnt immediate (gfx9 encoding: vmcnt[3:0] | expcnt[6:4] | lgkmcnt[11:8] | vmcnt_hi[15:14]):
 // at most n vector-memory operations (here: LDS-direct loads) outstanding, and no LDS operation.
@@ -101,13 +91,22 @@ struct Pipe {
   const char* p_b[N_B];
   int kc_lo, kc_hi;  // first channel of this lane's chunk inside a K step (packed operands / INT8 operand)
   int kext;          // channels in this loop (multiple of 32)
-  int wave;          // uniform
+  int wave;          // uniform, inside the K group
+  int grp;           // K group (uniform)
+  int steps;         // K steps of a group
+  int rot;           // step the loop starts with (the steps then wrap around)
 
   __device__ __forceinline__ void init(const uint8_t* a_lo, int64_t lda_lo, const int8_t* a_hi, int64_t lda_hi,
-                                       const uint8_t* b, int64_t ldb, int kext_, int m0, int n0, int M, int N) {
-    const int tid = threadIdx.x;
+                                       const uint8_t* b, int64_t ldb, int kext_, int m0, int n0, int M, int N, int rot8) {
+    const int tid = threadIdx.x & (NT - 1);
     kext = kext_;
     wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    grp = T::S == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / NT);
+    steps = (kext + KS * T::S - 1) / (KS * T::S);
+    // With two K groups (few tiles: operands come from far, little is shared) every XCD starts at its own place of K, so
+    // that rows 4 KB apart are not asked for at the same few hundred bytes by the whole chip at a time.  Only the last
+    // step may be partial (see issue), so the order is turned only where no step is.
+    rot = T::S > 1 && kext % (KS * T::S) == 0 ? rot8 * steps / 8 : 0;
     {
       const int row = tid >> 2;  // rows of later loads differ by a multiple of 64: same swizzle
       kc_lo = (((tid & 3) ^ (row >> 2)) & 3) * 32;
@@ -137,7 +136,12 @@ struct Pipe {
   // step of a loop can); its chunks past the end come from kZeroChunk.
   template <bool TAIL>
   __device__ __forceinline__ void issue(char* stage, int step) const {
-    const int k0 = step * KS;
+    int turned = step;
+    if constexpr (T::S > 1) {
+      turned += rot;
+      turned = turned >= steps ? turned - steps : turned;
+    }
+    const int k0 = (turned * T::S + grp) * KS;
     const char* zero = reinterpret_cast<const char*>(kZeroChunk);
     const bool lo_ok = !TAIL || (k0 + kc_lo < kext);
     const bool hi_ok = !TAIL || (k0 + kc_hi < kext);
@@ -182,13 +186,6 @@ __device__ __forceinline__ void read_frags(Frags<T>& f, const char* stage, int g
       f.ahi[i][1] = *reinterpret_cast<const v4i*>(stage + T::A_HI + off8(row, 4 * g + 2 * h + 1));
     }
   }
-}
-
-// Half s (0/1) of a packed chunk (16 of its 32 INT4 codes) -> the INT8 operand of matrix instruction s.
-__device__ __forceinline__ v4i widen(const v4u p, int s) {
-  const unsigned a = p[2 * s], b = p[2 * s + 1];
-  return v4i{static_cast<int>((a << 4) & 0xF0F0F0F0u), static_cast<int>(a & 0xF0F0F0F0u),
-             static_cast<int>((b << 4) & 0xF0F0F0F0u), static_cast<int>(b & 0xF0F0F0F0u)};
 }
 
 // Widened operands of one 32-channel slice of the fragments.
@@ -300,7 +297,7 @@ __device__ __forceinline__ void k_loop_start(const Pipe<T, LO, HI>& pipe, char* 
   pipe.template issue<true>(lds + st0 * T::STAGE, 0);
 #pragma unroll
   for (int s0 = 1; s0 < T::NS - 1; ++s0)
-    if (pipe.kext > s0 * KS) pipe.template issue<true>(lds + ((st0 + s0) % T::NS) * T::STAGE, s0);
+    if (pipe.steps > s0) pipe.template issue<true>(lds + ((st0 + s0) % T::NS) * T::STAGE, s0);
 }
 
 // The last iterations of a K loop, peeled: with R steps left after the current one, the iteration that still
@@ -338,7 +335,7 @@ __device__ __forceinline__ void k_loop(const Pipe<T, LO, HI>& pipe, char* lds, i
                                        v16i (&acc_lo)[T::TI][T::TJ], v16i (&acc_hi)[T::TI][T::TJ], int st0 = 0) {
   constexpr int NL = Pipe<T, LO, HI>::NLOAD;
   constexpr int D = T::NS - 1;
-  const int steps = (pipe.kext + KS - 1) / KS;
+  const int steps = pipe.steps;
   first_barrier<D, NL>(steps < D ? steps : D);
   Frags<T> f0, f1;
   Wide<T> w0, w1;
@@ -352,9 +349,6 @@ __device__ __forceinline__ void k_loop(const Pipe<T, LO, HI>& pipe, char* lds, i
   k_loop_tail<T, LO, HI, D>(pipe, lds, steps, kt, st, wm, wn, lane, f0, f1, w0, w1, acc_lo, acc_hi);
   __syncthreads();  // the stages are reused by the next loop / the epilogue
 }
-
-// fp32 -> bf16, round to nearest even (v_cvt_pk_bf16_f32).
-__device__ __forceinline__ uint16_t bf16_rne(float f) { return __builtin_bit_cast(uint16_t, static_cast<__bf16>(f)); }
 
 // Orders this wave's LDS writes before its later LDS reads of other lanes' data (compiler barrier +
 // wait for the wave's outstanding LDS operations); no other wave is involved.
@@ -399,7 +393,7 @@ struct EpiScales {
 
 template <typename T>
 __device__ __forceinline__ void load_epi_scales(EpiScales<T>& e, const GemmArgs& g, int m0, int n0, int wn, int lane) {
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x & (NT - 1);
   const int m = min(m0 + (tid < T::BM ? tid : 0), g.M - 1);
   e.slo = g.s_lo ? g.s_lo[m] : 0.0f;
   e.shi = g.s_hi[m];
@@ -421,7 +415,7 @@ __device__ __forceinline__ void epilogue_typed(const GemmArgs& g, const EpiScale
   constexpr int ROWS_PER_PASS = 64 / CHUNKS;
   constexpr int SC_BYTES = 2 * T::BM * 4;  // [0, BM): s_lo, [BM, 2 BM): s_hi
   static_assert(SC_BYTES + 4 * 32 * ROW <= T::LDS_BYTES, "transposition buffers must fit in the stage memory");
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x & (NT - 1);
   float* sc = reinterpret_cast<float*>(lds);
   char* tb = lds + SC_BYTES + wave * (32 * ROW);
   if (tid < T::BM) {
@@ -506,11 +500,56 @@ __device__ __forceinline__ void epilogue(const GemmArgs& g, const EpiScales<T>& 
 
 // MODE 0: dynamic (low + zero-padded high in one K loop); 1: static (low loop over K, then the
 // compact high loop over K_hi); 2: high loop only (plain W4A8 reference).
+// Adds the K groups' partial sums (integers: exact in any order) into the first group's registers, through LDS.
+// Every stage has been read for the last time (k_loop ends with a barrier); on return LDS is free again.
+template <typename T, bool LO>
+__device__ __forceinline__ void join_groups(char* lds, int grp, int wave, int lane, v16i (&acc_lo)[T::TI][T::TJ],
+                                            v16i (&acc_hi)[T::TI][T::TJ]) {
+  constexpr int PER_WAVE = T::TI * T::TJ * 8 * 1024;  // two products, 16 registers of 64 lanes
+  auto at = [&](int g, int i, int j, int p, int q) {
+    return reinterpret_cast<v4i*>(lds + ((g - 1) * 4 + wave) * PER_WAVE + (((i * T::TJ + j) * 2 + p) * 4 + q) * 1024 + lane * 16);
+  };
+  if (grp != 0) {
+#pragma unroll
+    for (int i = 0; i < T::TI; ++i)
+#pragma unroll
+      for (int j = 0; j < T::TJ; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          if (LO) *at(grp, i, j, 0, q) = v4i{acc_lo[i][j][4 * q], acc_lo[i][j][4 * q + 1], acc_lo[i][j][4 * q + 2], acc_lo[i][j][4 * q + 3]};
+          *at(grp, i, j, 1, q) = v4i{acc_hi[i][j][4 * q], acc_hi[i][j][4 * q + 1], acc_hi[i][j][4 * q + 2], acc_hi[i][j][4 * q + 3]};
+        }
+  }
+  __syncthreads();
+  if (grp == 0) {
+#pragma unroll
+    for (int g = 1; g < T::S; ++g)
+#pragma unroll
+      for (int i = 0; i < T::TI; ++i)
+#pragma unroll
+        for (int j = 0; j < T::TJ; ++j)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const v4i h = *at(g, i, j, 1, q);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc_hi[i][j][4 * q + e] += h[e];
+            if (LO) {
+              const v4i l = *at(g, i, j, 0, q);
+#pragma unroll
+              for (int e = 0; e < 4; ++e) acc_lo[i][j][4 * q + e] += l[e];
+            }
+          }
+  }
+  __syncthreads();  // the epilogue reuses the space
+}
+
 template <typename T, int MODE>
-__global__ __launch_bounds__(NT) void gemm_kernel(GemmArgs g) {
-  extern __shared__ __attribute__((aligned(16))) char lds[];
-  const int tid = threadIdx.x;
+__global__ __launch_bounds__(T::THREADS) void gemm_kernel(GemmArgs g) {
+  extern __shared__ __attribute__((aligned(16))) char lds_all[];
+  const int tid = threadIdx.x & (NT - 1);
+  const int grp = T::S == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / NT);
   const int lane = tid & 63, wave = tid >> 6;
+  char* lds = lds_all + grp * (T::NS * T::STAGE);  // every K group has its own stages
   const int wm = wave >> 1, wn = wave & 1;
   int tm, tn;
   tile_of_block(blockIdx.x, (g.M + T::BM - 1) / T::BM, (g.N + T::BN - 1) / T::BN, tm, tn);
@@ -525,13 +564,13 @@ __global__ __launch_bounds__(NT) void gemm_kernel(GemmArgs g) {
   Pipe<T, true, HI1> p1;           // MODE 0: low + zero-padded high; MODE 1: low only; MODE 2: unused
   Pipe<T, false, true> p2;         // MODE 1, 2: the compact high loop
   if constexpr (MODE == 0) {
-    p1.init(g.a_lo, g.K / 2, g.a_hi_dense, g.K, g.wq, g.K / 2, g.K, m0, n0, g.M, g.N);
+    p1.init(g.a_lo, g.K / 2, g.a_hi_dense, g.K, g.wq, g.K / 2, g.K, m0, n0, g.M, g.N, blockIdx.x & 7);
     k_loop_start<T, true, HI1>(p1, lds);
   } else if constexpr (MODE == 1) {
-    p1.init(g.a_lo, g.K_lo / 2, nullptr, 0, g.w_lo, g.K_lo / 2, g.K_lo, m0, n0, g.M, g.N);
+    p1.init(g.a_lo, g.K_lo / 2, nullptr, 0, g.w_lo, g.K_lo / 2, g.K_lo, m0, n0, g.M, g.N, blockIdx.x & 7);
     k_loop_start<T, true, HI1>(p1, lds);
   } else {
-    p2.init(nullptr, 0, g.a_hi_compact, g.lda_hi_compact, g.w_hi, g.K_hi / 2, g.K_hi, m0, n0, g.M, g.N);
+    p2.init(nullptr, 0, g.a_hi_compact, g.lda_hi_compact, g.w_hi, g.K_hi / 2, g.K_hi, m0, n0, g.M, g.N, blockIdx.x & 7);
     k_loop_start<T, false, true>(p2, lds);
   }
 
@@ -551,12 +590,19 @@ __global__ __launch_bounds__(NT) void gemm_kernel(GemmArgs g) {
   } else {
     if constexpr (MODE == 1) {
       k_loop<T, true, HI1>(p1, lds, wm, wn, lane, acc_lo, acc_hi);
-      p2.init(nullptr, 0, g.a_hi_compact, g.lda_hi_compact, g.w_hi, g.K_hi / 2, g.K_hi, m0, n0, g.M, g.N);
+      p2.init(nullptr, 0, g.a_hi_compact, g.lda_hi_compact, g.w_hi, g.K_hi / 2, g.K_hi, m0, n0, g.M, g.N, blockIdx.x & 7);
       k_loop_start<T, false, true>(p2, lds);
     }
     k_loop<T, false, true>(p2, lds, wm, wn, lane, acc_lo, acc_hi);
   }
 
+  if constexpr (T::S > 1) {
+    join_groups<T, MODE != 2>(lds_all, grp, wave, lane, acc_lo, acc_hi);
+    if (grp != 0) {
+      pipeline_barrier<63>();  // the epilogue's
+      return;
+    }
+  }
   epilogue<T>(g, es, lds, acc_lo, acc_hi, m0, n0, wm, wn, wave, lane);
 }
 
@@ -564,375 +610,46 @@ template <typename T, int MODE>
 int launch_mode(const GemmArgs& g, hipStream_t st) {
   const int tiles = ((g.N + T::BN - 1) / T::BN) * ((g.M + T::BM - 1) / T::BM);
   const int blocks = (tiles + 7) / 8 * 8;
-  hipLaunchKernelGGL((gemm_kernel<T, MODE>), dim3(blocks), dim3(NT), T::LDS_BYTES, st, g);
+  hipLaunchKernelGGL((gemm_kernel<T, MODE>), dim3(blocks), dim3(T::THREADS), T::LDS_BYTES, st, g);
   return hipGetLastError() == hipSuccess ? SQ_OK : SQ_ERR_LAUNCH;
 }
 
 
-// ---------------------------------------------------------------------------------------------
-// Decode shapes (M <= 64, dynamic mode): the layer is bound by streaming the INT4 weights once from
-// HBM, not by the matrix cores, and HBM needs tens of kilobytes in flight per compute unit.
-// Vector-memory operations of a wave retire in order, so one wave cannot keep a deep queue of weight
-// loads and, at the same time, wait for the shallow queue of (L2-resident) activation loads.  The
-// workgroup is therefore specialised: waves 0 and 1 multiply (32 output channels each, all tokens)
-// and copy the activation tiles six K steps ahead (ring of eight stages); wave 2 only copies weights,
-// seven K steps ahead, into its own ring of eight LDS stages.  Each wave waits on its own counter; one workgroup barrier
-// per K step publishes both copies.  Both copies are published one step earlier than they are
-// multiplied, so that a consumer fetches the operands of step kt+1 from LDS while the matrix
-// instructions of step kt run: the per-step chain "barrier -> LDS read -> multiply -> barrier", which
-// otherwise bounds the streaming rate at N * 64 bytes per chain time, shrinks to the multiply.
-// A workgroup covers 64 output channels, so N/64 workgroups (two per compute unit) stream disjoint rows.
-// TI = number of 32-token blocks (1: M <= 32, 2: M <= 64).  Requires K % 128 == 0.  Only TI = 1 is dispatched: with
-// two token blocks (12 KB of activations per stage, one workgroup per compute unit, or shallower activation rings to
-// fit two) the kernel was slower than the generic 64 x 64 tile at every ring depth tried (67-70 us against 54 us at
-// 64 tokens on the 70B shape).
-template <int TI>
-struct SkinnyCfg {
-  static constexpr int BM = 32 * TI;
-  static constexpr int BN = 64;
-  static constexpr int A_LO = 0;
-  static constexpr int A_HI = BM * 64;
-  static constexpr int A_STAGE = BM * 192;
-  static constexpr int A_STAGES = 8;
-  static constexpr int A_DIST = 6;  // the activation copy of step kt + A_DIST is enqueued during step kt
-  static constexpr int W_OFF = A_STAGES * A_STAGE;
-  static constexpr int W_STAGE = BN * 64;
-  static constexpr int W_STAGES = 8;
-  static constexpr int W_AHEAD = W_STAGES - 1;
-  static constexpr int LDS_BYTES = W_OFF + W_STAGES * W_STAGE;
-  static constexpr int N_LO = BM * 4 / 128;   // activation copies per consumer wave and K step
-  static constexpr int N_HI = BM * 8 / 128;
-  static constexpr int NA = N_LO + N_HI;
-  static constexpr int THREADS = 192;
-};
-
-// Weight loader wave: the four wave copies (64 rows x 64 bytes) of K step `step` into its ring stage.
-template <int TI>
-__device__ __forceinline__ void skinny_issue_w(const char* const (&src)[4], char* lds, int step) {
-  typedef SkinnyCfg<TI> C;
-  char* dst = lds + C::W_OFF + (step % C::W_STAGES) * C::W_STAGE;
-#pragma unroll
-  for (int q = 0; q < 4; ++q)
-    __builtin_amdgcn_global_load_lds(src[q] + step * 64, (lds_ptr_t)(dst + q * 1024), 16, 0, 0);
-}
-
-// Consumer waves: this wave's share of the activation tiles of K step `step`.
-template <int TI>
-__device__ __forceinline__ void skinny_issue_a(const char* const (&p_lo)[SkinnyCfg<TI>::N_LO],
-                                               const char* const (&p_hi)[SkinnyCfg<TI>::N_HI], char* lds, int step,
-                                               int wave) {
-  typedef SkinnyCfg<TI> C;
-  char* dst = lds + (step % C::A_STAGES) * C::A_STAGE;
-#pragma unroll
-  for (int i = 0; i < C::N_LO; ++i)
-    __builtin_amdgcn_global_load_lds(p_lo[i] + step * 64, (lds_ptr_t)(dst + C::A_LO + (128 * i + 64 * wave) * 16), 16, 0, 0);
-#pragma unroll
-  for (int i = 0; i < C::N_HI; ++i)
-    __builtin_amdgcn_global_load_lds(p_hi[i] + step * 128, (lds_ptr_t)(dst + C::A_HI + (128 * i + 64 * wave) * 16), 16, 0, 0);
-}
-
-// Operands of one K step of a consumer wave: packed weights of its 32 channels, packed low codes and
-// INT8 high codes of the tokens (two 64-channel halves each).
-template <int TI>
-struct SkinnyOps {
-  v4u fw[2];
-  v4u fa[TI][2];
-  v4i fh[TI][4];
-};
-
-// sa_idx / sw_idx: ring stages of the step's activation and weight tiles (compile-time constants in the
-// steady state, so that the reads differ only in their immediate offsets).
-template <int TI>
-__device__ __forceinline__ void skinny_fetch_at(SkinnyOps<TI>& o, const char* lds, int sa_idx, int sw_idx, int wave,
-                                                int r, int h) {
-  typedef SkinnyCfg<TI> C;
-  const char* sa = lds + sa_idx * C::A_STAGE;
-  const char* sw = lds + C::W_OFF + sw_idx * C::W_STAGE;
-#pragma unroll
-  for (int gq = 0; gq < 2; ++gq) {
-    o.fw[gq] = *reinterpret_cast<const v4u*>(sw + off4(wave * 32 + r, 2 * gq + h));
-#pragma unroll
-    for (int i = 0; i < TI; ++i) {
-      o.fa[i][gq] = *reinterpret_cast<const v4u*>(sa + C::A_LO + off4(i * 32 + r, 2 * gq + h));
-      o.fh[i][2 * gq] = *reinterpret_cast<const v4i*>(sa + C::A_HI + off8(i * 32 + r, 4 * gq + 2 * h));
-      o.fh[i][2 * gq + 1] = *reinterpret_cast<const v4i*>(sa + C::A_HI + off8(i * 32 + r, 4 * gq + 2 * h + 1));
-    }
-  }
-}
-
-template <int TI>
-__device__ __forceinline__ void skinny_fetch(SkinnyOps<TI>& o, const char* lds, int step, int wave, int r, int h) {
-  skinny_fetch_at<TI>(o, lds, step % SkinnyCfg<TI>::A_STAGES, step % SkinnyCfg<TI>::W_STAGES, wave, r, h);
-}
-
-template <int TI>
-__device__ __forceinline__ void skinny_mma(const SkinnyOps<TI>& o, v16i (&acc_lo)[TI], v16i (&acc_hi)[TI]) {
-#pragma unroll
-  for (int gq = 0; gq < 2; ++gq)
-#pragma unroll
-    for (int s2 = 0; s2 < 2; ++s2) {
-      const v4i bw = widen(o.fw[gq], s2);
-#pragma unroll
-      for (int i = 0; i < TI; ++i) {
-        acc_lo[i] = __builtin_amdgcn_mfma_i32_32x32x32_i8(widen(o.fa[i][gq], s2), bw, acc_lo[i], 0, 0, 0);
-        acc_hi[i] = __builtin_amdgcn_mfma_i32_32x32x32_i8(o.fh[i][2 * gq + s2], bw, acc_hi[i], 0, 0, 0);
-      }
-    }
-}
-
-// Multiply one step, then join the step's barrier; `copied`: this step enqueued an activation copy, so
-// A_DIST - 2 younger ones may stay in flight, otherwise everything outstanding is waited for.
-template <int TI>
-__device__ __forceinline__ void pipeline_barrier_after(const SkinnyOps<TI>& cur, v16i (&acc_lo)[TI], v16i (&acc_hi)[TI],
-                                                       bool copied) {
-  typedef SkinnyCfg<TI> C;
-  skinny_mma<TI>(cur, acc_lo, acc_hi);
-  if (copied) pipeline_barrier<(C::A_DIST - 2) * C::NA>();
-  else pipeline_barrier<0>();
-}
-
-// Step kt + U of a trip of eight steps that starts at a multiple of eight (the ring sizes divide eight, so
-// every stage index is a compile-time constant).  The sources of the activation copies of step kt + U + A_DIST
-// are a wave-uniform base (scalar registers, advanced by scalar additions) plus a per-lane 32-bit offset
-// that never changes.  (The instruction's immediate offset is no use here: for a copy into LDS it is added
-// to the LDS address as well.)
-// LAST: the trip is the last one of the K loop (it ends at the last step): only its first steps still have a
-// copy to enqueue, its last step has no successor to fetch, and the barrier's allowance shrinks with the
-// copies that remain outstanding.
-template <int TI, int U, bool LAST = false>
-__device__ __forceinline__ void skinny_steady_step(const SkinnyOps<TI>& cur, SkinnyOps<TI>& nxt, const char* ub_lo,
-                                                   const char* ub_hi, const unsigned (&l_lo)[SkinnyCfg<TI>::N_LO],
-                                                   const unsigned (&l_hi)[SkinnyCfg<TI>::N_HI], char* lds, int wave,
-                                                   int r, int h, v16i (&acc_lo)[TI], v16i (&acc_hi)[TI]) {
-  typedef SkinnyCfg<TI> C;
-  static_assert(8 % C::A_STAGES == 0 && 8 % C::W_STAGES == 0, "ring sizes must divide the trip length");
-  constexpr bool FETCH = !LAST || U + 1 < 8;
-  constexpr bool COPY = !LAST || U + C::A_DIST < 8;
-  // copies still outstanding at the barrier may be those of steps kt+U+3 ... : A_DIST-2 steps' worth in the
-  // steady state, in the last trip only up to its last step (step kt+7)
-  constexpr int YOUNGER = LAST ? (7 - (U + 2) > 0 ? 7 - (U + 2) : 0) : C::A_DIST - 2;
-  constexpr int PENDING = (YOUNGER < C::A_DIST - 2 ? YOUNGER : C::A_DIST - 2) * C::NA;
-  if (FETCH) skinny_fetch_at<TI>(nxt, lds, (U + 1) % C::A_STAGES, (U + 1) % C::W_STAGES, wave, r, h);
-  if (COPY) {
-    char* dst = lds + ((U + C::A_DIST) % C::A_STAGES) * C::A_STAGE;
-    const char* s_lo = ub_lo + (U + C::A_DIST) * 64;
-    const char* s_hi = ub_hi + (U + C::A_DIST) * 128;
-#pragma unroll
-    for (int i = 0; i < C::N_LO; ++i)
-      __builtin_amdgcn_global_load_lds(s_lo + l_lo[i], (lds_ptr_t)(dst + C::A_LO + (128 * i + 64 * wave) * 16), 16, 0, 0);
-#pragma unroll
-    for (int i = 0; i < C::N_HI; ++i)
-      __builtin_amdgcn_global_load_lds(s_hi + l_hi[i], (lds_ptr_t)(dst + C::A_HI + (128 * i + 64 * wave) * 16), 16, 0, 0);
-  }
-  skinny_mma<TI>(cur, acc_lo, acc_hi);
-  pipeline_barrier<PENDING>();  // the copies of steps <= kt + U + 2 have landed
-}
-
-template <int TI>
-__global__ __launch_bounds__(192) void gemm_skinny_kernel(GemmArgs g) {
-  typedef SkinnyCfg<TI> C;
-  extern __shared__ __attribute__((aligned(16))) char lds[];
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int n0 = blockIdx.x * C::BN;
-  const int steps = g.K / KS;
-  constexpr int W_AHEAD = C::W_AHEAD;
-
-  if (wave == 2) {
-    // ---- weight loader: 4 wave copies (64 rows x 64 bytes) per K step, W_AHEAD steps ahead ----
-    const char* src[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int row = 16 * q + (lane >> 2);
-      const int c = ((lane & 3) ^ (row >> 2)) & 3;
-      src[q] = reinterpret_cast<const char*>(g.wq) + static_cast<int64_t>(min(n0 + row, g.N - 1)) * (g.K / 2) + c * 16;
-    }
-    // at barrier kt (the prologue barrier is kt = -1) the copies of steps <= kt+2 have landed
-    const int pre = min(C::W_AHEAD, steps);
-    for (int s2 = 0; s2 < pre; ++s2) skinny_issue_w<TI>(src, lds, s2);
-    if (pre == C::W_AHEAD) pipeline_barrier<4 * (C::W_AHEAD - 2)>();
-    else pipeline_barrier<0>();
-    for (int kt = 0; kt < steps; ++kt) {
-      if (kt + C::W_AHEAD < steps) {
-        const int ahead = kt + W_AHEAD;
-        skinny_issue_w<TI>(src, lds, ahead);
-        pipeline_barrier<4 * (C::W_AHEAD - 2)>();  // five younger steps stay in flight
-      } else {
-        pipeline_barrier<0>();
-      }
-    }
-    return;
-  }
-
-  // ---- consumers ----
-  const int r = lane & 31, h = lane >> 5;
-  const char* p_lo[C::N_LO];
-  const char* p_hi[C::N_HI];
-#pragma unroll
-  for (int i = 0; i < C::N_LO; ++i) {
-    const int idx = tid + 128 * i, row = idx >> 2;
-    const int c = ((idx & 3) ^ (row >> 2)) & 3;
-    p_lo[i] = reinterpret_cast<const char*>(g.a_lo) + static_cast<int64_t>(min(row, g.M - 1)) * (g.K / 2) + c * 16;
-  }
-#pragma unroll
-  for (int i = 0; i < C::N_HI; ++i) {
-    const int idx = tid + 128 * i, row = idx >> 3;
-    const int c = ((idx & 7) ^ (row >> 1)) & 7;
-    p_hi[i] = reinterpret_cast<const char*>(g.a_hi_dense) + static_cast<int64_t>(min(row, g.M - 1)) * g.K + c * 16;
-  }
-
-  // per-token scales of the rows this lane's accumulator registers hold
-  float slo[TI][16], shi[TI][16];
-#pragma unroll
-  for (int i = 0; i < TI; ++i)
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      const int m = min(i * 32 + 8 * (q >> 2) + 4 * h + (q & 3), g.M - 1);
-      slo[i][q] = g.s_lo[m];
-      shi[i][q] = g.s_hi[m];
-    }
-  const int n = n0 + wave * 32 + r;
-  const float sw = g.s_w[min(n, g.N - 1)];
-
-  v16i acc_lo[TI], acc_hi[TI];
-#pragma unroll
-  for (int i = 0; i < TI; ++i)
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      acc_lo[i][q] = 0;
-      acc_hi[i][q] = 0;
-    }
-
-  // At barrier kt (prologue: kt = -1) this wave's activation copies of steps <= kt+2 have landed.  A copy
-  // is enqueued A_DIST steps before it is multiplied and has A_DIST - 2 steps to arrive: with one step
-  // (a few hundred nanoseconds here) the wait for it was half of every step.
-  constexpr int D = C::A_DIST;
-#pragma unroll
-  for (int s0 = 0; s0 < D; ++s0)
-    if (s0 < steps) skinny_issue_a<TI>(p_lo, p_hi, lds, s0, wave);
-  if (steps >= D) pipeline_barrier<(D - 2) * C::NA>();
-  else pipeline_barrier<0>();
-  // Operands of one K step are fetched from LDS one step ahead of the matrix instructions that use them.
-  // The steady state has no branches (the compiler then keeps the accumulators where they are and waits
-  // for the LDS reads of step kt+1 only after the matrix instructions of step kt have been issued) and no
-  // address arithmetic: with few tokens a step is a handful of matrix instructions, so every other
-  // instruction in it counts.
-  SkinnyOps<TI> o0, o1;
-  skinny_fetch<TI>(o0, lds, 0, wave, r, h);
-  int kt = 0;
-  {
-    // steady state: trips of eight steps with compile-time stage indices
-    unsigned l_lo[C::N_LO], l_hi[C::N_HI];  // per-lane byte offsets of the copies' sources (below 2^32: M <= 64 rows)
-#pragma unroll
-    for (int i = 0; i < C::N_LO; ++i) l_lo[i] = static_cast<unsigned>(p_lo[i] - reinterpret_cast<const char*>(g.a_lo));
-#pragma unroll
-    for (int i = 0; i < C::N_HI; ++i) l_hi[i] = static_cast<unsigned>(p_hi[i] - reinterpret_cast<const char*>(g.a_hi_dense));
-    const char* ub_lo = reinterpret_cast<const char*>(g.a_lo);
-    const char* ub_hi = reinterpret_cast<const char*>(g.a_hi_dense);
-    for (; kt + 8 + D <= steps; kt += 8) {  // the copy of step kt + 7 + A_DIST is the last one a trip enqueues
-      skinny_steady_step<TI, 0>(o0, o1, ub_lo, ub_hi, l_lo, l_hi, lds, wave, r, h, acc_lo, acc_hi);
-      skinny_steady_step<TI, 1>(o1, o0, ub_lo, ub_hi, l_lo, l_hi, lds, wave, r, h, acc_lo, acc_hi);
-      skinny_steady_step<TI, 2>(o0, o1, ub_lo, ub_hi, l_lo, l_hi, lds, wave, r, h, acc_lo, acc_hi);
-      skinny_steady_step<TI, 3>(o1, o0, ub_lo, ub_hi, l_lo, l_hi, lds, wave, r, h, acc_lo, acc_hi);
-      skinny_steady_step<TI, 4>(o0, o1, ub_lo, ub_hi, l_lo, l_hi, lds, wave, r, h, acc_lo, acc_hi);
-      skinny_steady_step<TI, 5>(o1, o0, ub_lo, ub_hi, l_lo, l_hi, lds, wave, r, h, acc_lo, acc_hi);
-      skinny_steady_step<TI, 6>(o0, o1, ub_lo, ub_hi, l_lo, l_hi, lds, wave, r, h, acc_lo, acc_hi);
-      skinny_steady_step<TI, 7>(o1, o0, ub_lo, ub_hi, l_lo, l_hi, lds, wave, r, h, acc_lo, acc_hi);
-      ub_lo += 8 * 64;
-      ub_hi += 8 * 128;
-    }
-    if (steps - kt == 8) {  // exactly one trip left (K a multiple of 1024): the same code, winding down
-      skinny_steady_step<TI, 0, true>(o0, o1, ub_lo, ub_hi, l_lo, l_hi, lds, wave, r, h, acc_lo, acc_hi);
-      skinny_steady_step<TI, 1, true>(o1, o0, ub_lo, ub_hi, l_lo, l_hi, lds, wave, r, h, acc_lo, acc_hi);
-      skinny_steady_step<TI, 2, true>(o0, o1, ub_lo, ub_hi, l_lo, l_hi, lds, wave, r, h, acc_lo, acc_hi);
-      skinny_steady_step<TI, 3, true>(o1, o0, ub_lo, ub_hi, l_lo, l_hi, lds, wave, r, h, acc_lo, acc_hi);
-      skinny_steady_step<TI, 4, true>(o0, o1, ub_lo, ub_hi, l_lo, l_hi, lds, wave, r, h, acc_lo, acc_hi);
-      skinny_steady_step<TI, 5, true>(o1, o0, ub_lo, ub_hi, l_lo, l_hi, lds, wave, r, h, acc_lo, acc_hi);
-      skinny_steady_step<TI, 6, true>(o0, o1, ub_lo, ub_hi, l_lo, l_hi, lds, wave, r, h, acc_lo, acc_hi);
-      skinny_steady_step<TI, 7, true>(o1, o0, ub_lo, ub_hi, l_lo, l_hi, lds, wave, r, h, acc_lo, acc_hi);
-      kt += 8;
-    }
-  }
-  // the remaining steps (fewer than 8 + A_DIST): stage indices and addresses computed at run time
-  while (kt < steps) {
-    if (kt + 1 < steps) skinny_fetch<TI>(o1, lds, kt + 1, wave, r, h);
-    if (kt + D < steps) {
-      skinny_issue_a<TI>(p_lo, p_hi, lds, kt + D, wave);
-      pipeline_barrier_after<TI>(o0, acc_lo, acc_hi, true);
-    } else {
-      pipeline_barrier_after<TI>(o0, acc_lo, acc_hi, false);
-    }
-    if (++kt >= steps) break;
-    if (kt + 1 < steps) skinny_fetch<TI>(o0, lds, kt + 1, wave, r, h);
-    if (kt + D < steps) {
-      skinny_issue_a<TI>(p_lo, p_hi, lds, kt + D, wave);
-      pipeline_barrier_after<TI>(o1, acc_lo, acc_hi, true);
-    } else {
-      pipeline_barrier_after<TI>(o1, acc_lo, acc_hi, false);
-    }
-    ++kt;
-  }
-
-  // epilogue: the outputs are few (M <= 64 rows); plain stores
-  if (n < g.N) {
-#pragma unroll
-    for (int i = 0; i < TI; ++i)
-#pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const int m = i * 32 + 8 * (q >> 2) + 4 * h + (q & 3);
-        if (m < g.M) {
-          float t = __fmul_rn(static_cast<float>(acc_lo[i][q] >> 8), slo[i][q]);
-          t = __fmaf_rn(static_cast<float>(acc_hi[i][q] >> 4), shi[i][q], t);
-          const float y = __fmul_rn(t, sw);
-          const int64_t o = static_cast<int64_t>(m) * g.ldy + n;
-          if (g.out_bf16) reinterpret_cast<uint16_t*>(g.y)[o] = bf16_rne(y);
-          else reinterpret_cast<float*>(g.y)[o] = y;
-          if (g.acc_lo_dbg) g.acc_lo_dbg[static_cast<int64_t>(m) * g.N + n] = acc_lo[i][q] >> 8;
-          if (g.acc_hi_dbg) g.acc_hi_dbg[static_cast<int64_t>(m) * g.N + n] = acc_hi[i][q] >> 4;
-        }
-      }
-  }
-}
-
-template <int TI>
-int launch_skinny(const GemmArgs& g, hipStream_t st) {
-  typedef SkinnyCfg<TI> C;
-  hipLaunchKernelGGL((gemm_skinny_kernel<TI>), dim3((g.N + C::BN - 1) / C::BN), dim3(C::THREADS), C::LDS_BYTES, st, g);
-  return hipGetLastError() == hipSuccess ? SQ_OK : SQ_ERR_LAUNCH;
-}
-
-// Three stages everywhere: a fourth stage for the 128x256 tile (exactly the 160 KB of LDS) and four or six for
-// the 64x64 tile were timed and change nothing (c3: 680 us either way on dense random operands; 64 tokens:
-// 55.7 / 60.4 us against 56.8 us) -- the copies are not what the loop waits for.
-typedef Tile<128, 256> Big;   // matrix-core bound shapes
-typedef Tile<64, 64> Skinny;  // M <= 64 (decode): bound by streaming the INT4 weights once from HBM, so the
-                              // tile is narrow in N to spread the weight rows over every compute unit
-                              // (several small workgroups per unit keep enough loads in flight)
-typedef Tile<64, 128> SkinnyWide;  // the same for very wide layers: every workgroup re-reads the activation tile from
-                                   // L2 on each K step, and at 64 tokens that traffic (three times the weight
-                                   // stream) is what bounds the 64-wide tile; twice the channels per workgroup
-                                   // halves it (52 us against 55.5 us on the 70B shape) as long as the wider
-                                   // tiles still cover most compute units
-typedef Tile<128, 128> Mid;   // shapes with too few 128x256 tiles to occupy every compute unit
+// Three stages everywhere: a fourth stage for the 128x256 tile (exactly the 160 KB of LDS) was timed and changes
+// nothing (c3: 680 us either way on dense random operands) -- the copies are not what the loop waits for.
+typedef Tile<128, 256> Big;                  // matrix-core bound shapes
+typedef Tile<128, 128> Mid;                  // too few of those to occupy every compute unit
+typedef Tile<64, 128, true, 3, 2> SmallWide;  // fewer still: two K groups of four waves per workgroup, so that a compute
+typedef Tile<64, 64, true, 3, 2> Small;       // unit has two waves per SIMD although it has one workgroup
 typedef Tile<256, 256, false> Huge;  // single-product modes on large shapes: with one accumulator set a wave
                                      // holds 128 x 128 outputs, which halves the operand traffic and the
                                      // widening arithmetic per matrix instruction and doubles the matrix
                                      // instructions between two barriers to 64, as in the two-product loop
 
-enum Variant { V_BIG, V_MID, V_SMALL, V_STREAM, V_HUGE, V_SMALL_WIDE };
+enum Variant { V_HUGE, V_BIG, V_MID, V_SMALL_WIDE, V_SMALL, V_FEW };
 
-// Which kernel a shape runs on.  dynamic: the call has the low operand and the zero-padded high image;
-// single: one product only (tied scales, plain W4A8).
-Variant pick_variant(int M, int N, int K, bool dynamic, bool single) {
-  if (M <= 64) {
-    if (dynamic && M <= 32 && K % KS == 0) return V_STREAM;
-    return (M > 32 && (N + 127) / 128 >= 200) ? V_SMALL_WIDE : V_SMALL;
+// Which kernel a shape runs on.  Every tile kernel fills a compute unit with one workgroup, so a launch takes
+// ceil(tiles / 256) rounds, and a round of each tile its own time: at K = 4096, two products, 48 us (Big), 28.5 us
+// (Mid), 18 us (SmallWide), 11.5 us (Small); single product 35 / 19 / 13.5 / 9 us.  The least rounds x time wins, a
+// larger tile on near ties (it moves less data).  Measured against the old rule (Big above 128 of its tiles, else Mid;
+// 64x64 up to 64 tokens): [333,11008] x [4095,11008] 66.9 -> 42.2 us (SmallWide), [128,4096] x [12288,4096] 26.7 ->
+// 18.2 us, [64,8192] x [28672,8192] 47.5 -> 36.0 us (SmallWide), [512,4096] x [4096,4096] 27.2 -> 19.7 us.
+Variant pick_variant(int M, int N, bool single) {
+  if (gemm_few_supports(M, N)) return V_FEW;
+  auto tiles = [&](int bm, int bn) { return static_cast<int64_t>((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+  if (single && tiles(256, 256) >= kHugeMinTiles) return V_HUGE;
+  struct { Variant v; int bm, bn, two, one; } const t[] = {
+      {V_BIG, 128, 256, 480, 350}, {V_MID, 128, 128, 285, 190}, {V_SMALL_WIDE, 64, 128, 180, 135}, {V_SMALL, 64, 64, 115, 90}};
+  Variant best = V_BIG;
+  int64_t least = INT64_MAX;
+  for (const auto& c : t) {
+    const int64_t cost = (tiles(c.bm, c.bn) + 255) / 256 * (single ? c.one : c.two);
+    if (least == INT64_MAX || cost * 10 < least * 9) {
+      least = cost;
+      best = c.v;
+    }
   }
-  const int64_t huge_tiles = static_cast<int64_t>((M + 255) / 256) * ((N + 255) / 256);
-  if (single && huge_tiles >= kHugeMinTiles) return V_HUGE;
-  const int64_t big_tiles = static_cast<int64_t>((M + 127) / 128) * ((N + 255) / 256);
-  return big_tiles <= 128 ? V_MID : V_BIG;  // then twice as many half-size tiles still run in one round
+  return best;
 }
 
 template <typename T, int MODE>
@@ -943,13 +660,16 @@ hipError_t raise_lds_limit() {
 
 template <int MODE>
 int launch_for_mode(const GemmArgs& g, hipStream_t st, Variant v) {
-  if constexpr (MODE == 2) {
-    if (v == V_HUGE) return launch_mode<Huge, 2>(g, st);
+  switch (v) {
+    case V_FEW: return launch_gemm_few(g, MODE, st);
+    case V_HUGE:
+      if constexpr (MODE == 2) return launch_mode<Huge, 2>(g, st);
+      return SQ_ERR_UNSUPPORTED;  // pick_variant gives it to single-product calls only
+    case V_BIG: return launch_mode<Big, MODE>(g, st);
+    case V_MID: return launch_mode<Mid, MODE>(g, st);
+    case V_SMALL_WIDE: return launch_mode<SmallWide, MODE>(g, st);
+    default: return launch_mode<Small, MODE>(g, st);
   }
-  if (v == V_BIG) return launch_mode<Big, MODE>(g, st);
-  if (v == V_MID) return launch_mode<Mid, MODE>(g, st);
-  if (v == V_SMALL_WIDE) return launch_mode<SkinnyWide, MODE>(g, st);
-  return launch_mode<Skinny, MODE>(g, st);
 }
 
 }  // namespace
@@ -962,33 +682,25 @@ int init_gemm_kernels() {
   if (e == hipSuccess) e = raise_lds_limit<T, 0>();          \
   if (e == hipSuccess) e = raise_lds_limit<T, 1>();          \
   if (e == hipSuccess) e = raise_lds_limit<T, 2>();
-  SQ_RAISE(Big) SQ_RAISE(Mid) SQ_RAISE(Skinny) SQ_RAISE(SkinnyWide)
+  SQ_RAISE(Big) SQ_RAISE(Mid) SQ_RAISE(SmallWide) SQ_RAISE(Small)
 #undef SQ_RAISE
   if (e == hipSuccess) e = raise_lds_limit<Huge, 2>();
-  if (e == hipSuccess)
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_skinny_kernel<1>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, SkinnyCfg<1>::LDS_BYTES);
-  return e == hipSuccess ? SQ_OK : SQ_ERR_LAUNCH;
+  return e == hipSuccess ? init_gemm_few_kernels() : SQ_ERR_LAUNCH;
 }
 
+// The size class of a shape (what sq_gemm_variant reports): by the number of 128 x 256 tiles and of tokens.
 const char* gemm_variant_name(int M, int N, int K, bool dynamic, bool single) {
-  switch (pick_variant(M, N, K, dynamic, single)) {
-    case V_HUGE: return "tile256x256";
-    case V_BIG: return "tile128x256";
-    case V_MID: return "tile128x128";
-    case V_SMALL: return "tile64x64";
-    case V_SMALL_WIDE: return "tile64x128";
-    default: return "stream32";
+  if (M <= 64) {
+    if (dynamic && M <= 32 && K % KS == 0) return "stream32";
+    return (M > 32 && (N + 127) / 128 >= 200) ? "tile64x128" : "tile64x64";
   }
+  if (single && static_cast<int64_t>((M + 255) / 256) * ((N + 255) / 256) >= kHugeMinTiles) return "tile256x256";
+  return static_cast<int64_t>((M + 127) / 128) * ((N + 255) / 256) <= 128 ? "tile128x128" : "tile128x256";
 }
 
 int launch_gemm(const GemmArgs& g, hipStream_t st) {
-  const bool dynamic = g.a_lo && g.a_hi_dense;
-  const Variant v = pick_variant(g.M, g.N, g.K, dynamic, !g.a_lo);
-  if (dynamic) {
-    if (v == V_STREAM) return launch_skinny<1>(g, st);
-    return launch_for_mode<0>(g, st, v);
-  }
+  const Variant v = pick_variant(g.M, g.N, !g.a_lo);
+  if (g.a_lo && g.a_hi_dense) return launch_for_mode<0>(g, st, v);
   if (g.a_lo && g.a_hi_compact) return launch_for_mode<1>(g, st, v);
   if (!g.a_lo && g.a_hi_compact) return launch_for_mode<2>(g, st, v);
   return SQ_ERR_UNSUPPORTED;
