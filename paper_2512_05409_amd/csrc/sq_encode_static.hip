@@ -8,13 +8,17 @@
 // channel order), next to `hi_val`, the high codes of the high channels only -- the two operands of the two
 // products, each contiguous, so that the low product runs over K_lo channels instead of K.
 //
-// A workgroup walks over token rows.  Per workgroup, once: two index tables in LDS, built from the mask:
-// the channel of every compact low position and of every compact high position.  Per row: the row is copied
-// from HBM into LDS by coalesced LDS-direct loads; the work is output-centric: every thread owns whole dwords
-// of the outputs (8 low codes, 4 high codes, or 8 dense low codes), gathers their source values from the staged
-// row through the tables into registers (taking the row maxima of both parts on the way), and once the scales
-// are known quantises from the registers, so every store is coalesced and the staged row is free early: the
-// next row's copy runs under the reduction, the quantisation and the stores of this one.
+// A workgroup walks over token rows, which LDS-direct loads copy into two row buffers, one row ahead.  A thread owns the
+// same 16-byte pieces (8 channels) of every row, so everything that depends on the mask only is worked out once and
+// stays in registers: which of the 8 channels are low, the byte permutation that moves their codes together, where in the
+// compact row they go, and the LDS offsets of the high channels' values.  Per row a thread reads its pieces (taking the
+// row maxima on the way) and, once the workgroup's maxima are combined, quantises them to 8 bytes, moves the low ones
+// together (v_perm_b32), packs them to nibbles and ORs them into the compact row in LDS, which leaves in 16-byte stores.
+// Bounds: HBM (2 bytes read and 0.5 (1 - k/b) + k/b written per element) and vector arithmetic (about 7 instructions
+// per element) are close to each other: another row costs 5.9 ns at 11008 channels (4.8 TB/s), launch, tables and the
+// first row about 10 us.  Gathering every low code by its own 16-bit LDS read instead was bound by those reads and their
+// bank conflicts, and building the index table one bank per thread took most of a short call: [4096,11008] 43.6 -> 34.6
+// us, [4096,4096] 40.2 -> 17.4 us, [2048,14336] 41.4 -> 24.2 us, [8,11008] 15.3 -> 9.2 us (calls back to back).
 #include "sq_encode_common.h"
 
 namespace sq {
@@ -24,7 +28,6 @@ using namespace enc;
 
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned short u16x4 __attribute__((ext_vector_type(4)));
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
@@ -34,156 +37,209 @@ __device__ __forceinline__ uint32_t pk_max_u16(uint32_t a, uint32_t b) {
   return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b)));
 }
 
-constexpr int NT = 256;
-
 struct GatherArgs {
   const uint16_t* x;
   int64_t ldx;
-  int M, K, B, kt, G;
+  int M, K, B, kt;
   int K_hi, K_lo;
+  int bufs;               // row buffers: 2, or 1 where two do not fit
   const uint32_t* mask;   // [K/32]
   uint8_t* d_lo;          // [M, K/2] dense low codes, or null
   uint8_t* lo_compact;    // [M, K_lo/2], or null
   int8_t* hi_val;         // [M, K_hi]
   float* s_lo;
   float* s_hi;
-  int row_bytes_padded;   // LDS bytes of the staged row (K * 2 rounded up to 4096)
   float q_hi, q_lo;       // largest code magnitudes of the two parts (127 and 7 for the 8/4 pair)
 };
 
-// MAXI: output dwords of each kind a thread owns at most (K / 8 / 256 rounded up).
-template <int MAXI>
-__global__ __launch_bounds__(NT) void encode_static_gather_kernel(GatherArgs a) {
+// At most n vector-memory operations outstanding.  n is known at run time only (and the same for the whole wave);
+// the instruction takes a constant, so n is rounded down to one of a few.
+template <int N>
+__device__ __forceinline__ void wait_vm_at_most(int n) {
+  if constexpr (N > 0) {
+    if (n < N) {
+      wait_vm_at_most<N - (N > 8 ? 4 : 1)>(n);
+      return;
+    }
+  }
+  __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
+}
+// Workgroup barrier that orders LDS traffic only (__syncthreads() would also drain the copies in flight).
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt((15) | (7 << 4) | (0 << 8) | (3 << 14));  // lgkmcnt(0)
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+__device__ __forceinline__ uint32_t lds_u16(const char* lds, uint32_t addr) {
+  return *reinterpret_cast<const uint16_t*>(lds + addr);
+}
+
+// *p |= v.  (Written out: before an atomic on LDS the compiler waits for every LDS-direct load in flight.)
+__device__ __forceinline__ void lds_or(uint32_t* p, uint32_t v) {
+  const uint32_t at = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) uint32_t*)p));
+  asm volatile("ds_or_b32 %0, %1" ::"v"(at), "v"(v) : "memory");
+}
+
+// The low bytes of the rounded products of 8 consecutive channels (4 packed bf16 pairs), two dwords.
+__device__ __forceinline__ void quant8(const uint32_t* pairs, float inv, uint32_t& b03, uint32_t& b47) {
+  b03 = b47 = 0;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const uint32_t w = pairs[e >> 1];
+    const float xf = __uint_as_float((e & 1) ? (w & 0xFFFF0000u) : (w << 16));
+    uint32_t& d = e < 4 ? b03 : b47;
+    d = __builtin_amdgcn_alignbit(__float_as_uint(__fadd_rn(__fmul_rn(xf, inv), kRoundMagic)), d, 8);
+  }
+}
+
+// LDS: the row buffers [K * 2], the compact row [K_lo / 2 + 16], the mask [K / 8].
+// NT: threads; IT: pieces a thread owns at most (with 3, registers for three workgroups per compute unit, which is what
+// LDS holds of such rows: 34.6 us with three, 35.9 us with two at 11008 channels).  COMPACT / DENSE: lo_compact / d_lo are written.
+template <int NT, int IT, bool COMPACT, bool DENSE>
+__global__ __launch_bounds__(NT, IT == 3 ? 6 : 1) void encode_static_gather_kernel(GatherArgs a) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
-  __shared__ uint32_t amax_sh[2][2];
-  char* row = lds;                                                                  // staged bf16 row
-  uint16_t* src_lo = reinterpret_cast<uint16_t*>(lds + a.row_bytes_padded);         // [K_lo] channel of compact low position
-  uint16_t* src_hi = src_lo + ((a.K_lo + 7) & ~7);                                  // [K_hi]
-  uint32_t* mask_sh = reinterpret_cast<uint32_t*>(src_hi + ((a.K_hi + 7) & ~7));    // [K/32] the channel mask
+  constexpr int NWAVE = NT / 64;
+  __shared__ __attribute__((aligned(16))) uint32_t part[2][NWAVE];  // row maxima of the waves: high << 16 | low
+  const int row_bytes = 2 * a.K;
+  uint32_t* out_sh = reinterpret_cast<uint32_t*>(lds + a.bufs * row_bytes);
+  uint32_t* mask_sh = out_sh + a.K_lo / 8 + 4;
+  uint32_t* lut = mask_sh + a.K / 32;  // [256][2] byte permutation of every mask byte
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-  // ---- once per workgroup: the mask and the two index tables ----
-  for (int w = tid; w < a.K / 32; w += NT) mask_sh[w] = a.mask[w];
-  if (tid < 4) amax_sh[tid >> 1][tid & 1] = 0;
-  const int nlo = a.B - a.kt;
-  for (int g = tid; g < a.G; g += NT) {
-    int cl = 0, ch = 0;
-    for (int i = 0; i < a.B; ++i) {
-      const int j = g * a.B + i;
-      const bool hi = (a.mask[j >> 5] >> (j & 31)) & 1u;
-      if (hi) {
-        if (ch < a.kt) src_hi[g * a.kt + ch] = static_cast<uint16_t>(j);  // a malformed mask cannot write out of range
-        ++ch;
-      } else {
-        if (cl < nlo) src_lo[g * nlo + cl] = static_cast<uint16_t>(j);
-        ++cl;
-      }
-    }
-    for (; ch < a.kt; ++ch) src_hi[g * a.kt + ch] = static_cast<uint16_t>(g * a.B);
-    for (; cl < nlo; ++cl) src_lo[g * nlo + cl] = static_cast<uint16_t>(g * a.B);
-  }
-
-  const int chunks = a.K / 8;                 // 16-byte pieces of a row
-  const int n_copy = (chunks + NT - 1) / NT;  // copy instructions per thread and row
-  const int n_lo = a.lo_compact ? a.K_lo / 8 : 0, n_hi = a.K_hi / 4, n_dense = a.d_lo ? chunks : 0;
+  const int chunks = a.K / 8;  // 16-byte pieces of a row
+  const int out16 = a.K_lo / 32, n_hi = a.K_hi / 4;  // 16-byte pieces of the compact row, dwords of high codes
+  const int it_p = (chunks + NT - 1) / NT, it_hi = (n_hi + NT - 1) / NT;  // uniform
+  // instructions of this wave over n items dealt to the threads in turn: those that have a lane with an item
+  auto mine = [&](int n) { return (n - wave * 64 + NT - 1) / NT; };
+  const int n_copy = mine(chunks), n_store = mine(n_hi) + (COMPACT ? mine(out16) : 0) + (DENSE ? mine(chunks) : 0);
 
   // thread t copies pieces t, t + 256, ... (1 KB of consecutive memory per wave instruction)
-  auto stage_row = [&](int64_t m) {
+  auto stage_row = [&](int64_t m, int buf) {
     const char* xrow = reinterpret_cast<const char*>(a.x + m * a.ldx);
-    for (int i = 0; i < n_copy; ++i) {
-      int c = i * NT + tid;
-      c = c < chunks ? c : chunks - 1;  // the tail re-reads the last piece (it lands in the padding)
-      const char* src = xrow + c * 16;
-      __builtin_amdgcn_global_load_lds(src, (lds_ptr_t)(row + (i * NT + wave * 64) * 16), 16, 0, 0);
+    char* row = lds + buf * row_bytes;
+#pragma unroll
+    for (int i = 0; i < IT; ++i) {
+      const int c = i * NT + tid;
+      if (c < chunks) __builtin_amdgcn_global_load_lds(xrow + c * 16, (lds_ptr_t)(row + (i * NT + wave * 64) * 16), 16, 0, 0);
     }
   };
 
-  if (blockIdx.x < a.M) stage_row(blockIdx.x);
-  int par = 0;
-  for (int64_t m = blockIdx.x; m < a.M; m += gridDim.x, par ^= 1) {
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_waitcnt((0 & 15) | (7 << 4) | (15 << 8) | (0 << 14));  // vmcnt(0): the copy has landed
-    __syncthreads();                                                           // barrier A
-    if (tid < 2) amax_sh[par ^ 1][tid] = 0;  // the next row's maxima (last read before barrier A)
+  const int64_t stride = gridDim.x;
+  if (a.bufs == 2) stage_row(blockIdx.x, 0);  // the grid has at most M workgroups
 
-    // ---- gather: every thread fetches the source values of the output dwords it owns, packed two bf16 per
-    // register, and takes the maxima of their magnitudes on the way ----
-    // (Threads whose dword index is past the end gather the last dword again instead of being masked off:
-    // without branches all the gathers of a thread are in flight together and it waits once.)
-    uint32_t vlo[MAXI][4], vhi[MAXI][2], vde[MAXI][4];
-    uint32_t mx_hi = 0, mx_lo = 0;  // packed: two 15-bit magnitudes per register
-    const int it_lo = (n_lo + NT - 1) / NT, it_hi = (n_hi + NT - 1) / NT, it_de = (n_dense + NT - 1) / NT;  // uniform
-    {
+  // ---- once per workgroup ----
+  for (int w = tid; w < a.K / 32; w += NT) mask_sh[w] = a.mask[w];
+  for (int w = tid; w < a.K_lo / 8 + 4; w += NT) out_sh[w] = 0;
+  uint16_t* tab_hi = reinterpret_cast<uint16_t*>(lds + (a.bufs - 1) * row_bytes);  // channels of the high positions, in the last buffer
+  for (int w = tid; w < a.K_hi / 2; w += NT) reinterpret_cast<uint32_t*>(tab_hi)[w] = 0;  // (a malformed mask leaves gaps)
+  if (COMPACT && tid < 256) {  // moves the bytes whose bit of tid is clear together; 0x0C selects a zero byte
+    uint64_t s = 0x0C0C0C0C0C0C0C0Cull;
+    for (int e = 7; e >= 0; --e)
+      if (!((tid >> e) & 1)) s = (s << 8) | static_cast<uint64_t>(e);
+    lut[2 * tid] = static_cast<uint32_t>(s);
+    lut[2 * tid + 1] = static_cast<uint32_t>(s >> 32);
+  }
+  lds_barrier();
+  const int nlo = a.B - a.kt, lgB = 31 - __clz(a.B);
+  // of the thread's pieces: byte permutation, first compact position, mask bits, magnitude bits of the low channels
+  uint32_t sel[IT][2], at[IT], mb[IT], keep[IT][4];
 #pragma unroll
-      for (int i = 0; i < MAXI; ++i) {
-        if (i >= it_lo) break;
-        const int j = min(i * NT + tid, n_lo - 1);
-        const u16x8 idx = *reinterpret_cast<const u16x8*>(src_lo + 8 * j);
+  for (int i = 0; i < IT; ++i) {
+    sel[i][0] = sel[i][1] = 0x0C0C0C0Cu;  // a thread past the end of the row ORs zeros
+    at[i] = mb[i] = keep[i][0] = keep[i][1] = keep[i][2] = keep[i][3] = 0;
+    const int c = i * NT + tid;
+    if (c < chunks) {
+      const int ch = 8 * c, bank = ch >> lgB, w0 = bank << (lgB - 5), w1 = ch >> 5;
+      int hi = 0;  // high channels of the bank before this piece
+      for (int w = w0; w < w1; ++w) hi += __popc(mask_sh[w]);
+      const uint32_t word = mask_sh[w1];
+      hi += __popc(word & ((1u << (ch & 31)) - 1u));
+      mb[i] = (word >> (ch & 31)) & 0xFFu;
+      // (a malformed mask: positions past the bank's end stay inside the row and its spare dwords)
+      at[i] = static_cast<uint32_t>(bank * nlo + min((ch & (a.B - 1)) - hi, nlo));
+      if (COMPACT) {
+        sel[i][0] = lut[2 * mb[i]];
+        sel[i][1] = lut[2 * mb[i] + 1];
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        keep[i][q] = ((mb[i] >> (2 * q)) & 1u ? 0u : 0x7FFFu) | ((mb[i] >> (2 * q + 1)) & 1u ? 0u : 0x7FFF0000u);
+      for (uint32_t left = mb[i]; left != 0 && hi < a.kt; left &= left - 1, ++hi)
+        tab_hi[bank * a.kt + hi] = static_cast<uint16_t>(ch + __ffs(static_cast<int>(left)) - 1);
+    }
+  }
+  lds_barrier();
+  uint32_t ahi[IT][4];  // LDS offsets inside a row buffer
+#pragma unroll
+  for (int i = 0; i < IT; ++i) {
+    if (i < it_hi) {
+      const u16x4 v = *reinterpret_cast<const u16x4*>(tab_hi + 4 * min(i * NT + tid, n_hi - 1));
+#pragma unroll
+      for (int e = 0; e < 4; ++e) ahi[i][e] = 2u * v[e];
+    }
+  }
+  lds_barrier();
+  if (a.bufs == 1) stage_row(blockIdx.x, 0);
+  else if (blockIdx.x + stride < a.M) stage_row(blockIdx.x + stride, 1);
+
+  int it = 0;
+  for (int64_t m = blockIdx.x; m < a.M; m += stride, ++it) {
+    // Operations younger than this row's copy: the later rows' copies, and the stores of as many rows as there are buffers
+    asm volatile("" ::: "memory");
+    wait_vm_at_most<32>((a.bufs == 2 && m + stride < a.M ? n_copy : 0) + min(it, a.bufs) * n_store);
+    lds_barrier();  // barrier A: every wave's part of the row is there
+    const int buf = a.bufs == 2 ? it & 1 : 0;
+    const char* row = lds + buf * row_bytes;
+
+    // ---- the thread's pieces, the high values it owns, and the maxima of their magnitudes (packed: two 15-bit
+    // magnitudes per register) ----
+    uint32_t v[IT][4], vhi[IT][2];
+    uint32_t mx_hi = 0, mx_lo = 0;
+#pragma unroll
+    for (int i = 0; i < IT; ++i) {
+      if (i < it_p) {
+        const u32x4 t = *reinterpret_cast<const u32x4*>(row + min(i * NT + tid, chunks - 1) * 16);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[i][q] = t[q];
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < IT; ++i) {
+      if (i < it_hi) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) vhi[i][q] = lds_u16(row, ahi[i][2 * q]) | (lds_u16(row, ahi[i][2 * q + 1]) << 16);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < IT; ++i) {
+      if (i < it_p) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          const uint32_t x0 = *reinterpret_cast<const uint16_t*>(row + 2 * idx[2 * q]);
-          const uint32_t x1 = *reinterpret_cast<const uint16_t*>(row + 2 * idx[2 * q + 1]);
-          vlo[i][q] = x0 | (x1 << 16);
-          mx_lo = pk_max_u16(mx_lo, vlo[i][q] & 0x7FFF7FFFu);
+          mx_lo = pk_max_u16(mx_lo, v[i][q] & keep[i][q]);
         }
       }
-    }
+      if (i < it_hi) {
 #pragma unroll
-    for (int i = 0; i < MAXI; ++i) {
-      if (i >= it_hi) break;
-      const int j = min(i * NT + tid, n_hi - 1);
-      const u16x4 idx = *reinterpret_cast<const u16x4*>(src_hi + 4 * j);
-#pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        const uint32_t x0 = *reinterpret_cast<const uint16_t*>(row + 2 * idx[2 * q]);
-        const uint32_t x1 = *reinterpret_cast<const uint16_t*>(row + 2 * idx[2 * q + 1]);
-        vhi[i][q] = x0 | (x1 << 16);
-        mx_hi = pk_max_u16(mx_hi, vhi[i][q] & 0x7FFF7FFFu);
+        for (int q = 0; q < 2; ++q) mx_hi = pk_max_u16(mx_hi, vhi[i][q] & 0x7FFF7FFFu);
       }
     }
+    uint32_t mx = (umax(mx_hi & 0xFFFFu, mx_hi >> 16) << 16) | umax(mx_lo & 0xFFFFu, mx_lo >> 16);
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) mx = pk_max_u16(mx, static_cast<uint32_t>(__shfl_xor(static_cast<int>(mx), off, 64)));
+    if (lane == 0) part[it & 1][wave] = mx;
+    lds_barrier();  // barrier B: the row has been read for the last time, the waves' maxima are there
+    if (m + a.bufs * stride < a.M) stage_row(m + a.bufs * stride, buf);
     {
+      mx = 0;
 #pragma unroll
-      for (int i = 0; i < MAXI; ++i) {
-        if (i >= it_de) break;
-        const int j = min(i * NT + tid, n_dense - 1);
-        const u32x4 v = *reinterpret_cast<const u32x4*>(row + j * 16);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) vde[i][q] = v[q];
+      for (int w = 0; w < NWAVE; w += 4) {
+        const u32x4 p = *reinterpret_cast<const u32x4*>(&part[it & 1][w]);
+        mx = pk_max_u16(pk_max_u16(mx, pk_max_u16(p[0], p[1])), pk_max_u16(p[2], p[3]));
       }
     }
-    // without lo_compact the low maximum comes from the dense pieces
-    if (!a.lo_compact) {
-#pragma unroll
-      for (int i = 0; i < MAXI; ++i) {
-        const int j = i * NT + tid;
-        if (j < n_dense) {
-          const uint32_t mb = (mask_sh[j >> 2] >> (8 * (j & 3))) & 0xFFu;
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const uint32_t w = vde[i][e >> 1];
-            const uint32_t mag = (e & 1) ? ((w >> 16) & 0x7FFFu) : (w & 0x7FFFu);
-            mx_lo = umax(mx_lo, ((mb >> e) & 1u) ? 0u : mag);
-          }
-        }
-      }
-    }
-    __syncthreads();  // barrier B: the staged row has been read for the last time
-    if (m + gridDim.x < a.M) stage_row(m + gridDim.x);  // the next row streams in under the rest of this one
-
-    mx_hi = umax(mx_hi & 0xFFFFu, mx_hi >> 16);
-    mx_lo = umax(mx_lo & 0xFFFFu, mx_lo >> 16);
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      mx_hi = umax(mx_hi, static_cast<uint32_t>(__shfl_xor(static_cast<int>(mx_hi), off, 64)));
-      mx_lo = umax(mx_lo, static_cast<uint32_t>(__shfl_xor(static_cast<int>(mx_lo), off, 64)));
-    }
-    if (lane == 0) {
-      atomicMax(&amax_sh[par][0], mx_hi);
-      atomicMax(&amax_sh[par][1], mx_lo);
-    }
-    __syncthreads();  // barrier C
-    const uint32_t ah = amax_sh[par][0], al = amax_sh[par][1];
+    const uint32_t ah = mx >> 16, al = mx & 0xFFFFu;
     const float amax_hi = __uint_as_float(ah << 16), amax_lo = __uint_as_float(al << 16);
     const float inv_hi = ah ? a.q_hi / amax_hi : 0.0f;
     const float inv_lo = al ? a.q_lo / amax_lo : 0.0f;
@@ -192,15 +248,24 @@ __global__ __launch_bounds__(NT) void encode_static_gather_kernel(GatherArgs a) 
       a.s_lo[m] = al ? amax_lo / a.q_lo : 1.0f;
     }
 
-    // ---- quantise from the registers: whole output dwords per thread, coalesced stores ----
-    uint32_t* dst_lo = reinterpret_cast<uint32_t*>(a.lo_compact + m * (a.K_lo / 2));
+    // ---- quantise from the registers ----
     uint32_t* dst_hi = reinterpret_cast<uint32_t*>(a.hi_val + m * a.K_hi);
     uint32_t* dst_de = reinterpret_cast<uint32_t*>(a.d_lo + m * (a.K / 2));
 #pragma unroll
-    for (int i = 0; i < MAXI; ++i) {
-      const int j = i * NT + tid;
-      if (j < n_lo) dst_lo[j] = quant_lo8(vlo[i], inv_lo);
-      if (j < n_hi) {
+    for (int i = 0; i < IT; ++i) {
+      if (COMPACT && i < it_p) {
+        uint32_t b03, b47;
+        quant8(v[i], inv_lo, b03, b47);
+        uint32_t t0 = __builtin_amdgcn_perm(b47, b03, sel[i][0]) & 0x0F0F0F0Fu;
+        uint32_t t1 = __builtin_amdgcn_perm(b47, b03, sel[i][1]) & 0x0F0F0F0Fu;
+        t0 |= t0 >> 4;
+        t1 |= t1 >> 4;
+        const uint64_t x = static_cast<uint64_t>(__builtin_amdgcn_perm(t1, t0, 0x06040200u)) << (4 * (at[i] & 7));
+        uint32_t* o = out_sh + (at[i] >> 3);
+        lds_or(o, static_cast<uint32_t>(x));
+        lds_or(o + 1, static_cast<uint32_t>(x >> 32));
+      }
+      if (i < it_hi) {
         uint32_t acc = 0;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -209,36 +274,69 @@ __global__ __launch_bounds__(NT) void encode_static_gather_kernel(GatherArgs a) 
           const float r = __fadd_rn(__fmul_rn(xf, inv_hi), kRoundMagic);
           acc = __builtin_amdgcn_alignbit(__float_as_uint(r), acc, 8);
         }
-        dst_hi[j] = acc;
+        if (i * NT + tid < n_hi) dst_hi[i * NT + tid] = acc;
       }
-      if (j < n_dense) {
-        const uint32_t mb = (mask_sh[j >> 2] >> (8 * (j & 3))) & 0xFFu;
-        dst_de[j] = quant_lo8(vde[i], inv_lo) & ~spread_bits_to_nibbles(mb);
+      if (DENSE && i * NT + tid < chunks)
+        dst_de[i * NT + tid] = quant_lo8(v[i], inv_lo) & ~spread_bits_to_nibbles(mb[i]);
+    }
+    if constexpr (COMPACT) {
+      lds_barrier();  // barrier C: the compact row is complete
+      u32x4* dst = reinterpret_cast<u32x4*>(a.lo_compact + m * (a.K_lo / 2));
+#pragma unroll
+      for (int i = 0; i < IT; ++i) {
+        const int j = i * NT + tid;
+        if (j < out16) {
+          u32x4* o = reinterpret_cast<u32x4*>(out_sh + 4 * j);
+          dst[j] = *o;
+          *o = u32x4{0u, 0u, 0u, 0u};  // for the next row, whose codes arrive after two more barriers
+        }
       }
     }
   }
 }
 
+constexpr size_t kLdsLimit = 158 * 1024;
+
+size_t gather_lds_bytes(const sq_params& p, int bufs) {
+  const size_t K_lo = p.K - static_cast<size_t>(p.K / p.bank) * p.topk;
+  return static_cast<size_t>(bufs) * 2 * p.K + K_lo / 2 + 16 + p.K / 8 + 2048;
+}
+
+// Threads and pieces per thread: rows of up to 4096, 8192, 12288, 16384 and 40960 channels.  Eight waves: with four and
+// twice the pieces [4096,4096] took 24.5 us instead of 17 us (the fixed work per wave and row is spread over less).
+#define SQ_STATIC_CFG(X) X(512, 1) X(512, 2) X(512, 3) X(512, 4) X(512, 10)
+
+template <int NT, int IT>
+int launch_it(const GatherArgs& a, int blocks, size_t lds, hipStream_t st) {
+  if (!a.d_lo) hipLaunchKernelGGL((encode_static_gather_kernel<NT, IT, true, false>), dim3(blocks), dim3(NT), lds, st, a);
+  else if (!a.lo_compact) hipLaunchKernelGGL((encode_static_gather_kernel<NT, IT, false, true>), dim3(blocks), dim3(NT), lds, st, a);
+  else hipLaunchKernelGGL((encode_static_gather_kernel<NT, IT, true, true>), dim3(blocks), dim3(NT), lds, st, a);
+  return hipGetLastError() == hipSuccess ? SQ_OK : SQ_ERR_LAUNCH;
+}
+
+template <int NT, int IT, bool COMPACT, bool DENSE>
+hipError_t raise_static() {
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(encode_static_gather_kernel<NT, IT, COMPACT, DENSE>),
+                             hipFuncAttributeMaxDynamicSharedMemorySize, kLdsLimit);
+}
+
 }  // namespace
 
-// Rows up to 65535 channels (16-bit table entries) whose stage and tables fit in LDS.
+// Rows up to 65535 channels (16-bit table entries); the bound on the LDS is that of two buffers' worth per channel.
 bool encode_static_gather_supports(const sq_params& p) {
-  if (p.K > 20 * NT * 8) return false;  // 40960: output dwords per thread; also keeps the tables' entries in 16 bits
+  if (p.K > 40960) return false;  // pieces per thread; also keeps the table's entries in 16 bits
   const size_t row = (static_cast<size_t>(p.K) * 2 + 4095) / 4096 * 4096;
   return row + static_cast<size_t>(p.K) * 2 + p.K / 8 + 64 <= 150 * 1024;
 }
 
-static size_t gather_lds_bytes(int K) {
-  const size_t row = (static_cast<size_t>(K) * 2 + 4095) / 4096 * 4096;
-  return row + static_cast<size_t>(K) * 2 + K / 8 + 64;  // staged row, two 16-bit tables, the mask
-}
-
 int init_encode_static_kernels() {
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(encode_static_gather_kernel<8>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, 150 * 1024 + 64);
-  if (e == hipSuccess)
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(encode_static_gather_kernel<20>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, 150 * 1024 + 64);
+  hipError_t e = hipSuccess;
+#define X(NT, IT)                                                      \
+  if (e == hipSuccess) e = raise_static<NT, IT, true, false>();        \
+  if (e == hipSuccess) e = raise_static<NT, IT, false, true>();        \
+  if (e == hipSuccess) e = raise_static<NT, IT, true, true>();
+  SQ_STATIC_CFG(X)
+#undef X
   return e == hipSuccess ? SQ_OK : SQ_ERR_LAUNCH;
 }
 
@@ -251,8 +349,7 @@ int launch_encode_static_gather(const sq_params& p, const uint16_t* x, int64_t l
   a.K = p.K;
   a.B = p.bank;
   a.kt = p.topk;
-  a.G = p.K / p.bank;
-  a.K_hi = a.G * p.topk;
+  a.K_hi = (p.K / p.bank) * p.topk;
   a.K_lo = p.K - a.K_hi;
   a.mask = mask;
   a.d_lo = out.d_lo;
@@ -262,17 +359,17 @@ int launch_encode_static_gather(const sq_params& p, const uint16_t* x, int64_t l
   a.s_hi = out.scale_hi;
   a.q_hi = code_max(p.h_high, 8);
   a.q_lo = code_max(p.h_low, 4);
-  a.row_bytes_padded = static_cast<int>((static_cast<size_t>(p.K) * 2 + 4095) / 4096 * 4096);
-  const size_t lds = gather_lds_bytes(p.K);
-  const int cus = device_compute_units();
-  int per_cu = static_cast<int>(160 * 1024 / (lds + 256));
-  if (per_cu < 1) per_cu = 1;
-  if (per_cu > 4) per_cu = 4;
-  const int64_t cap = static_cast<int64_t>(cus) * per_cu;
+  a.bufs = gather_lds_bytes(p, 2) <= kLdsLimit ? 2 : 1;
+  const size_t lds = gather_lds_bytes(p, a.bufs);
+  // as many workgroups as are resident at once, each walking over its share of the rows
+  const int64_t per_cu = static_cast<int64_t>(160 * 1024 / (lds + 64)), most = p.K <= 8192 ? 4 : p.K <= 12288 ? 3 : 2;
+  const int64_t cap = device_compute_units() * (per_cu > most ? most : per_cu);
   const int blocks = static_cast<int>(p.M < cap ? p.M : cap);
-  if (p.K <= 8 * NT * 8) hipLaunchKernelGGL(encode_static_gather_kernel<8>, dim3(blocks), dim3(NT), lds, st, a);
-  else hipLaunchKernelGGL(encode_static_gather_kernel<20>, dim3(blocks), dim3(NT), lds, st, a);
-  return hipGetLastError() == hipSuccess ? SQ_OK : SQ_ERR_LAUNCH;
+#define X(NT, IT) \
+  if (p.K <= NT * IT * 8) return launch_it<NT, IT>(a, blocks, lds, st);
+  SQ_STATIC_CFG(X)
+#undef X
+  return SQ_ERR_UNSUPPORTED;
 }
 
 }  // namespace sq
