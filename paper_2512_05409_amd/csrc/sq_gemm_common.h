@@ -27,5 +27,25 @@ __device__ __forceinline__ v4i widen(const v4u p, int s) {
 // fp32 -> bf16, round to nearest even (v_cvt_pk_bf16_f32).
 __device__ __forceinline__ uint16_t bf16_rne(float f) { return __builtin_bit_cast(uint16_t, static_cast<__bf16>(f)); }
 
+// Maps the linear workgroup id to a tile so that (a) the workgroups resident on one XCD at a time
+// (ids congruent mod 8 go to the same XCD) cover a compact 4 x 8 patch of tiles and share operand
+// tiles in that XCD's L2, and (b) every XCD walks its own contiguous range of the tile order.
+__device__ __forceinline__ void tile_of_block(int id, int tiles_m, int tiles_n, int& tm, int& tn) {
+  const int total = tiles_m * tiles_n;
+  const int per_xcd = (total + 7) / 8;
+  const int lin = (id & 7) * per_xcd + (id >> 3);  // position in the tile order
+  if (lin >= total) {  // the grid is rounded up to a multiple of 8: the overhang does nothing
+    tm = -1;
+    tn = -1;
+    return;
+  }
+  constexpr int BAND = 4;  // tile rows walked together
+  const int band = lin / (BAND * tiles_n);
+  const int within = lin - band * (BAND * tiles_n);
+  const int rows_here = min(BAND, tiles_m - band * BAND);
+  tn = within / rows_here;
+  tm = band * BAND + within - tn * rows_here;
+}
+
 }  // namespace gemm
 }  // namespace sq

@@ -8,14 +8,14 @@
 // bank's two products (exact, on v_mfma_i32_32x32x32_i8) are converted and folded into an fp32 accumulator in a
 // fixed order.  That is 5 vector instructions per accumulator register per bank against 4 matrix instructions
 // per bank of 64 channels: this layer is bound by vector arithmetic, not by the matrix cores.
-// The kernels here are written for correctness against the oracle (single-buffered LDS tiles, 64 x 64 outputs per
-// workgroup), not tuned: this file is the first working form of the second workload, not its final one.
-#include "sq_device.h"
+#include "sq_gemm_common.h"
 
 namespace sq {
 namespace {
 
-typedef unsigned int v4u __attribute__((ext_vector_type(4)));
+using gemm::lds_ptr_t;
+using gemm::v2u;
+using gemm::v4u;
 constexpr float kMagic = 12582912.0f;  // 1.5 * 2^23: adding it leaves rne(x) in the low mantissa bits
 
 __device__ __forceinline__ int rne_code(float x, float inv) {
@@ -125,38 +125,53 @@ __global__ __launch_bounds__(256) void wsq_prepack_kernel(int N, int K, int B, i
 }
 
 // ---- run time: plain per-token symmetric quantisation of the activations (Section 4.1: the operand that is not
-// in SQ-format is plain INTy), codes written in the byte order of the weight images.  One workgroup per row. ----
+// in SQ-format is plain INTy), codes written in the byte order of the weight images.  One workgroup per row; a row of up
+// to 2048 IT channels is read once and kept in registers between its maximum and its codes (IT = 0: read twice).  Bound
+// by HBM, 3 bytes per element (read twice, [4096,4096] took 20.9 us). ----
+template <int IT>
 __global__ __launch_bounds__(256) void quantize_act_kernel(const uint16_t* __restrict__ x, int64_t ldx, int K, float q,
                                                            int8_t* __restrict__ a8, float* __restrict__ a_scale) {
-  __shared__ uint32_t amax_sh;
-  if (threadIdx.x == 0) amax_sh = 0;
-  __syncthreads();
+  __shared__ uint32_t wave_max[4];
   const int64_t m = blockIdx.x;
   const uint16_t* row = x + m * ldx;
+  const int tid = threadIdx.x, n = K / 8;
+  v4u keep[IT > 0 ? IT : 1];
   uint32_t mx = 0;
-  for (int c = threadIdx.x; c < K / 8; c += 256) {
-    const uint4 v = *reinterpret_cast<const uint4*>(row + c * 8);
-    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-    for (int e = 0; e < 4; ++e) mx = max(mx, max(w[e] & 0x7FFFu, (w[e] >> 16) & 0x7FFFu));
+  auto piece_max = [&](const v4u& v) {
+    for (int e = 0; e < 4; ++e) mx = max(mx, max(v[e] & 0x7FFFu, (v[e] >> 16) & 0x7FFFu));
+  };
+  if constexpr (IT > 0) {
+#pragma unroll
+    for (int i = 0; i < IT; ++i) keep[i] = *reinterpret_cast<const v4u*>(row + min(i * 256 + tid, n - 1) * 8);
+#pragma unroll
+    for (int i = 0; i < IT; ++i) piece_max(keep[i]);
+  } else {
+    for (int c = tid; c < n; c += 256) piece_max(*reinterpret_cast<const v4u*>(row + c * 8));
   }
-  atomicMax(&amax_sh, mx);
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) mx = max(mx, static_cast<uint32_t>(__shfl_xor(static_cast<int>(mx), off, 64)));
+  if ((tid & 63) == 0) wave_max[tid >> 6] = mx;
   __syncthreads();
-  const uint32_t am = amax_sh;
+  const uint32_t am = max(max(wave_max[0], wave_max[1]), max(wave_max[2], wave_max[3]));
   const float amax = __uint_as_float(am << 16);
   const float inv = am ? __fdiv_rn(q, amax) : 0.0f;
-  if (threadIdx.x == 0) a_scale[m] = am ? __fdiv_rn(amax, q) : 1.0f;
-  const int iq = static_cast<int>(q);
-  for (int c = threadIdx.x; c < K / 8; c += 256) {
-    const uint4 v = *reinterpret_cast<const uint4*>(row + c * 8);
-    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-    uint32_t ev = 0, od = 0;  // codes of the even / odd channels of the group
+  if (tid == 0) a_scale[m] = am ? __fdiv_rn(amax, q) : 1.0f;
+  auto piece_codes = [&](const v4u& v, int c) {
+    uint32_t ev = 0, od = 0;  // codes of the even / odd channels of the group, the first one ends in the low byte
+#pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const int c0 = min(max(rne_code(__uint_as_float(w[e] << 16), inv), -iq), iq);
-      const int c1 = min(max(rne_code(__uint_as_float(w[e] & 0xFFFF0000u), inv), -iq), iq);
-      ev |= static_cast<uint32_t>(c0 & 0xFF) << (8 * e);
-      od |= static_cast<uint32_t>(c1 & 0xFF) << (8 * e);
+      const float x0 = __fmul_rn(__uint_as_float(v[e] << 16), inv), x1 = __fmul_rn(__uint_as_float(v[e] & 0xFFFF0000u), inv);
+      ev = __builtin_amdgcn_alignbit(__float_as_uint(__fadd_rn(__builtin_amdgcn_fmed3f(x0, -q, q), kMagic)), ev, 8);
+      od = __builtin_amdgcn_alignbit(__float_as_uint(__fadd_rn(__builtin_amdgcn_fmed3f(x1, -q, q), kMagic)), od, 8);
     }
-    *reinterpret_cast<uint2*>(a8 + m * K + c * 8) = make_uint2(ev, od);
+    *reinterpret_cast<v2u*>(a8 + m * K + c * 8) = v2u{ev, od};
+  };
+  if constexpr (IT > 0) {
+#pragma unroll
+    for (int i = 0; i < IT; ++i)
+      if (i * 256 + tid < n) piece_codes(keep[i], i * 256 + tid);
+  } else {
+    for (int c = tid; c < n; c += 256) piece_codes(*reinterpret_cast<const v4u*>(row + c * 8), c);
   }
 }
 
@@ -181,7 +196,8 @@ struct WsqGemmArgs {
   int32_t* acc_hi_dbg;
 };
 
-// 64 tokens x 64 output channels per workgroup, four waves of 32 x 32; one bank per trip.
+// The per-bank products themselves (tests): 64 tokens x 64 output channels per workgroup, four waves of 32 x 32; one
+// bank per trip, single-buffered.
 template <int B>
 __global__ __launch_bounds__(256) void wsq_gemm_kernel(WsqGemmArgs g) {
   __shared__ __attribute__((aligned(16))) char s_a[64 * B];       // activation codes of the bank
@@ -269,17 +285,29 @@ __global__ __launch_bounds__(256) void wsq_gemm_kernel(WsqGemmArgs g) {
 }
 
 // ---- the throughput kernel ----
-// 128 tokens x 128 output channels per workgroup, four waves of 64 x 64 (2 x 2 tiles of 32 x 32: 64 fp32 and 128
-// integer accumulator registers per lane).  A K step is 64 channels; its operands (8 KB of activation codes, 8 KB of
-// INT8 high weights, 4 KB of packed low weights, 1 KB of the bank's scales) are copied into one of three LDS stages
-// by LDS-direct loads two steps ahead, rows XOR-swizzled as in the activation-SQ kernel.  After the last step of a
-// bank the two integer tiles are folded into the fp32 accumulators (5 vector instructions per register): that fold,
-// not the matrix instructions, is what bounds the kernel; with two workgroups per compute unit one wave's fold
-// overlaps the other's matrix instructions.
-typedef __attribute__((address_space(3))) void* lds_ptr_t;
-constexpr int W2_A = 0, W2_WH = 8192, W2_WL = 16384, W2_SC = 20480, W2_STAGE = 21504, W2_NS = 3;
+// 32 MW tokens x 128 output channels per workgroup, 2 MW waves of 32 x 64.  The operands of a bank (BPB stages of 64
+// channels: activation codes, INT8 high weights, packed low weights; and the bank's scales) are copied into a ring of LDS
+// stages by LDS-direct loads, R - 1 banks ahead, rows XOR-swizzled as in the activation-SQ kernel.  A wave multiplies one
+// 32 x 32 tile of the bank (4 * BPB matrix instructions into 32 integer registers) and folds it into its fp32
+// accumulators (5 vector instructions per register) before it starts on the next tile: with so few registers four waves
+// share a SIMD, and one wave's fold runs under the others' matrix instructions.  That fold bounds the kernel: 1280 cycles
+// per 64 x 64 outputs and bank against 512 * BPB of matrix instructions.  With four waves of 64 x 64 per workgroup (all
+// four tiles' integer registers live, two waves per SIMD) the two hardly overlapped:
+// [4096,4096] x [22016,4096] 1317 -> 1187 us with banks of 64, 1079 -> 888 us with banks of 128; [300,4096] x [4096,4096]
+// 96 -> 66 us; [8,4096] x [12288,4096] 106 -> 66 us (the single-buffered kernel ran there).
+template <int BPB_, int MW_>
+struct W2 {
+  static constexpr int BPB = BPB_, MW = MW_;
+  static constexpr int BM = 32 * MW, THREADS = 128 * MW;
+  static constexpr int A = 0, WH = BM * 64, WL = WH + 8192, STAGE = WL + 4096;  // a 64-channel stage
+  static constexpr int SC = BPB * STAGE, BANK = SC + 1024;                      // the bank's scales: 128 low, 128 high
+  static constexpr int FIT = (MW == 4 ? 80 : 160) * 1024 / BANK;  // two workgroups per compute unit, or one
+  static constexpr int R = FIT > 4 ? 4 : (FIT < 2 ? 2 : FIT);
+  static constexpr int EPI = 2 * MW * 32 * (64 * 4 + 16);  // the epilogue's buffers
+  static constexpr int LDS_BYTES = R * BANK > EPI ? R * BANK : EPI;
+  static_assert(LDS_BYTES <= 160 * 1024, "LDS");
+};
 
-__device__ __forceinline__ int w2_off4(int row, int c) { return (row << 6) + (((c ^ (row >> 2)) & 3) << 4); }  // 64-byte rows
 __device__ __forceinline__ int w2_off2(int row, int c) { return (row << 5) + (((c ^ (row >> 3)) & 1) << 4); }  // 32-byte rows
 
 template <int N>
@@ -291,7 +319,7 @@ __device__ __forceinline__ void w2_wait() {  // at most N vector-memory operatio
 }
 
 struct Wsq2Args {
-  int M, N, K, G, Npad, bpb;  // bpb: 64-channel steps per bank (1 or 2)
+  int M, N, K, G, Npad;
   const int8_t* a8;
   const float* a_scale;
   const uint8_t* lo_clean;
@@ -303,143 +331,142 @@ struct Wsq2Args {
   int out_bf16;
 };
 
-__global__ __launch_bounds__(256, 2) void wsq_gemm2_kernel(Wsq2Args g) {
+template <typename OutT>
+__device__ __forceinline__ void w2_epilogue(const Wsq2Args& g, char* tb, const float (&f)[2][16], int m0, int n0, int lane) {
+  // the wave's 32 x 64 outputs through LDS, then 16 bytes per lane
+  constexpr int ESZ = sizeof(OutT), ROW = 64 * ESZ + 16, PER16 = 16 / ESZ, CHUNKS = 64 / PER16, ROWS = 64 / CHUNKS;
+  const int r = lane & 31, h = lane >> 5;
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    const int rl = 8 * (q >> 2) + 4 * h + (q & 3);
+    const float sa = g.a_scale[min(m0 + rl, g.M - 1)];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const float y = __fmul_rn(f[j][q], sa);
+      OutT* dst = reinterpret_cast<OutT*>(tb + rl * ROW) + j * 32 + r;
+      if constexpr (ESZ == 2) *dst = gemm::bf16_rne(y);
+      else *dst = y;
+    }
+  }
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt((15) | (7 << 4) | (0 << 8) | (3 << 14));  // lgkmcnt(0): the buffer is the wave's own
+  asm volatile("" ::: "memory");
+  const bool vec_ok = (g.ldy % PER16) == 0;
+#pragma unroll
+  for (int p0 = 0; p0 < 32; p0 += ROWS) {
+    const int rl = p0 + lane / CHUNKS, ch = lane % CHUNKS, m = m0 + rl, n = n0 + ch * PER16;
+    if (m < g.M && n < g.N) {
+      OutT* dst = reinterpret_cast<OutT*>(g.y) + static_cast<int64_t>(m) * g.ldy + n;
+      if (vec_ok && n + PER16 <= g.N) {
+        *reinterpret_cast<v4u*>(dst) = *reinterpret_cast<const v4u*>(tb + rl * ROW + ch * 16);
+      } else {
+        const OutT* src = reinterpret_cast<const OutT*>(tb + rl * ROW + ch * 16);
+        for (int q = 0; q < PER16 && n + q < g.N; ++q) dst[q] = src[q];
+      }
+    }
+  }
+}
+
+template <typename C>
+__global__ __launch_bounds__(C::THREADS, 4) void wsq_gemm2_kernel(Wsq2Args g) {
+  constexpr int BPB = C::BPB, MW = C::MW;
   extern __shared__ __attribute__((aligned(16))) char lds[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
   const int r = lane & 31, h = lane >> 5;
-  const int m0 = blockIdx.y * 128, n0 = blockIdx.x * 128;
-  const int steps = g.K / 64;
+  int tm, tn;
+  gemm::tile_of_block(blockIdx.x, (g.M + C::BM - 1) / C::BM, (g.N + 127) / 128, tm, tn);
+  if (tm < 0) return;
+  const int m0 = tm * C::BM, n0 = tn * 128;
 
-  // per-lane sources of the copies of one step (at k = 0)
-  const char* pa[2];
-  const char* pwh[2];
-  const char* pwl;
-  for (int i = 0; i < 2; ++i) {
-    const int idx = tid + 256 * i, row = idx >> 2, c = ((idx & 3) ^ (row >> 2)) & 3;
-    pa[i] = reinterpret_cast<const char*>(g.a8) + static_cast<int64_t>(min(m0 + row, g.M - 1)) * g.K + c * 16;
-    pwh[i] = reinterpret_cast<const char*>(g.hi_dense) + static_cast<int64_t>(min(n0 + row, g.N - 1)) * g.K + c * 16;
-  }
+  // per-lane sources of the copies of one stage (at k = 0).  Every wave copies its share of the activations; the weights
+  // and the scales are dealt to some of them.
+  constexpr int WL0 = MW == 4 ? 0 : 8, WSC = WL0 + 4;  // first wave of the low weights (four of them), wave of the scales
+  const bool has_wh = wave < 8, has_wl = wave >= WL0 && wave < WL0 + 4, has_sc = wave == WSC;
+  const char *pa, *pwh, *pwl, *psc;
   {
-    const int row = tid >> 1, c = ((tid & 1) ^ (row >> 3)) & 1;
-    pwl = reinterpret_cast<const char*>(g.lo_clean) + static_cast<int64_t>(min(n0 + row, g.N - 1)) * (g.K / 2) + c * 16;
+    const int row = tid >> 2, c = ((tid & 3) ^ (row >> 2)) & 3;
+    pa = reinterpret_cast<const char*>(g.a8) + static_cast<int64_t>(min(m0 + row, g.M - 1)) * g.K + c * 16;
+    const int rowh = (tid & 511) >> 2;
+    pwh = reinterpret_cast<const char*>(g.hi_dense) + static_cast<int64_t>(min(n0 + rowh, g.N - 1)) * g.K + c * 16;
+    const int row2 = (tid & 255) >> 1, c2 = ((tid & 1) ^ (row2 >> 3)) & 1;
+    pwl = reinterpret_cast<const char*>(g.lo_clean) + static_cast<int64_t>(min(n0 + row2, g.N - 1)) * (g.K / 2) + c2 * 16;
+    // lanes 0-31 fetch the low scales of the workgroup's 128 channels, lanes 32-63 the high ones
+    psc = reinterpret_cast<const char*>(lane < 32 ? g.s_lo_t : g.s_hi_t) + (static_cast<int64_t>(n0) + (lane & 31) * 4) * 4;
   }
-  // scales of a bank for the workgroup's 128 channels: lanes 0-31 of wave 0 the low ones, lanes 32-63 the high ones
-  const char* psc = reinterpret_cast<const char*>(lane < 32 ? g.s_lo_t : g.s_hi_t) + (static_cast<int64_t>(n0) + (lane & 31) * 4) * 4;
-
-  auto issue = [&](int step) {
-    char* st = lds + (step % W2_NS) * W2_STAGE;
-    for (int i = 0; i < 2; ++i) {
-      const char* src = pa[i] + step * 64;
-      __builtin_amdgcn_global_load_lds(src, (lds_ptr_t)(st + W2_A + (256 * i + 64 * wave) * 16), 16, 0, 0);
+  auto issue = [&](int bank) {
+    char* base = lds + (bank % C::R) * C::BANK;
+#pragma unroll
+    for (int b = 0; b < BPB; ++b) {
+      const int step = bank * BPB + b;
+      char* st = base + b * C::STAGE;
+      __builtin_amdgcn_global_load_lds(pa + step * 64, (lds_ptr_t)(st + C::A + 1024 * wave), 16, 0, 0);
+      if (has_wh) __builtin_amdgcn_global_load_lds(pwh + step * 64, (lds_ptr_t)(st + C::WH + 1024 * wave), 16, 0, 0);
+      if (has_wl) __builtin_amdgcn_global_load_lds(pwl + step * 32, (lds_ptr_t)(st + C::WL + 1024 * (wave - WL0)), 16, 0, 0);
     }
-    for (int i = 0; i < 2; ++i) {
-      const char* src = pwh[i] + step * 64;
-      __builtin_amdgcn_global_load_lds(src, (lds_ptr_t)(st + W2_WH + (256 * i + 64 * wave) * 16), 16, 0, 0);
-    }
-    {
-      const char* src = pwl + step * 32;
-      __builtin_amdgcn_global_load_lds(src, (lds_ptr_t)(st + W2_WL + 64 * wave * 16), 16, 0, 0);
-    }
-    if (wave == 0) {
-      const char* src = psc + static_cast<int64_t>(step / g.bpb) * g.Npad * 4;
-      __builtin_amdgcn_global_load_lds(src, (lds_ptr_t)(st + W2_SC), 16, 0, 0);
+    if (has_sc) {
+      const char* src = psc + static_cast<int64_t>(bank) * g.Npad * 4;
+      __builtin_amdgcn_global_load_lds(src, (lds_ptr_t)(base + C::SC), 16, 0, 0);
     }
   };
+  const int per_bank = BPB * (1 + has_wh + has_wl) + has_sc;  // copies of this wave per bank: 1 ... 6
+#pragma unroll
+  for (int b = 0; b < C::R - 1; ++b)
+    if (b < g.G) issue(b);
 
-  issue(0);
-  if (steps > 1) issue(1);
-
-  float f[2][2][16];
-  v16i acc_lo[2][2], acc_hi[2][2];
+  float f[2][16];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int j = 0; j < 2; ++j)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int q = 0; q < 16; ++q) f[i][j][q] = 0.0f;
+    for (int q = 0; q < 16; ++q) f[j][q] = 0.0f;
   const v16i zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
 
-  for (int kt = 0; kt < steps; ++kt) {
-    // step kt has landed when at most the copies of step kt+1 are outstanding (wave 0 issues one more per step)
-    if (kt + 1 < steps) {
-      if (wave == 0) w2_wait<6>();
-      else w2_wait<5>();
-    } else {
-      w2_wait<0>();
-    }
-    // the stage of step kt-1 is free now (every wave has passed its fold / its last read of it before this barrier)
-    if (kt + 2 < steps) issue(kt + 2);
-    const char* st = lds + (kt % W2_NS) * W2_STAGE;
-    v4i a[2][2], wh[2][2];
-    v4u wl[2];
+  for (int bank = 0; bank < g.G; ++bank) {
+    // this wave's copies of the bank have landed when at most those of the R - 2 banks after it are in flight
+    if (C::R == 2 || bank + C::R - 2 >= g.G) w2_wait<0>();
+    else if (per_bank >= 3) w2_wait<(C::R - 2) * 3>();
+    else if (per_bank == 2) w2_wait<(C::R - 2) * 2>();
+    else w2_wait<C::R - 2>();
+    // the stages of bank - 1 are free: every wave has read them for the last time before this barrier
+    if (bank + C::R - 1 < g.G) issue(bank + C::R - 1);
+    const char* st0 = lds + (bank % C::R) * C::BANK;
+    const float* sc = reinterpret_cast<const float*>(st0 + C::SC) + 64 * wn + r;
+    v4i a[BPB][2];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int b = 0; b < BPB; ++b)
 #pragma unroll
-      for (int s2 = 0; s2 < 2; ++s2) a[i][s2] = *reinterpret_cast<const v4i*>(st + W2_A + w2_off4(64 * wm + 32 * i + r, 2 * h + s2));
+      for (int s2 = 0; s2 < 2; ++s2)
+        a[b][s2] = *reinterpret_cast<const v4i*>(st0 + b * C::STAGE + C::A + gemm::off4(32 * wm + r, 2 * h + s2));
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
+      v16i acc_lo = zero, acc_hi = zero;
+      const float sl = sc[32 * j], sh = sc[128 + 32 * j];
 #pragma unroll
-      for (int s2 = 0; s2 < 2; ++s2) wh[j][s2] = *reinterpret_cast<const v4i*>(st + W2_WH + w2_off4(64 * wn + 32 * j + r, 2 * h + s2));
-      wl[j] = *reinterpret_cast<const v4u*>(st + W2_WL + w2_off2(64 * wn + 32 * j + r, h));
-    }
-    const bool first = kt % g.bpb == 0;  // first step of a bank: its products start from zero (no registers to clear)
+      for (int b = 0; b < BPB; ++b) {
+        const char* st = st0 + b * C::STAGE;
+        const v4u wl = *reinterpret_cast<const v4u*>(st + C::WL + w2_off2(64 * wn + 32 * j + r, h));
 #pragma unroll
-    for (int s2 = 0; s2 < 2; ++s2)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const v4i wlo = widen_half(wl[j], s2);
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          if (s2 == 0 && first) {
-            acc_lo[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[i][s2], wlo, zero, 0, 0, 0);
-            acc_hi[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[i][s2], wh[j][s2], zero, 0, 0, 0);
-          } else {
-            acc_lo[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[i][s2], wlo, acc_lo[i][j], 0, 0, 0);
-            acc_hi[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[i][s2], wh[j][s2], acc_hi[i][j], 0, 0, 0);
-          }
+        for (int s2 = 0; s2 < 2; ++s2) {
+          const v4i wh = *reinterpret_cast<const v4i*>(st + C::WH + gemm::off4(64 * wn + 32 * j + r, 2 * h + s2));
+          acc_lo = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[b][s2], widen_half(wl, s2), acc_lo, 0, 0, 0);
+          acc_hi = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[b][s2], wh, acc_hi, 0, 0, 0);
         }
       }
-    if ((kt + 1) % g.bpb == 0) {  // last step of a bank: fold its two integer tiles into the fp32 accumulators
-      const float* sc = reinterpret_cast<const float*>(st + W2_SC);
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const float sl = sc[64 * wn + 32 * j + r], sh = sc[128 + 64 * wn + 32 * j + r];
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-          for (int q = 0; q < 16; ++q) {
-            // the widened low weights carry a factor 16, which the transposed low scales carry inverted (sl is
-            // s_lo / 16: float(16 a) * (s / 16) is float(a) * s bit for bit while s / 16 is a normal number)
-            float t = __fmul_rn(static_cast<float>(acc_lo[i][j][q]), sl);
-            t = __fmaf_rn(static_cast<float>(acc_hi[i][j][q]), sh, t);
-            f[i][j][q] = __fadd_rn(f[i][j][q], t);
-          }
+      for (int q = 0; q < 16; ++q) {
+        // the widened low weights carry a factor 16, which the transposed low scales carry inverted (sl is
+        // s_lo / 16: float(16 a) * (s / 16) is float(a) * s bit for bit while s / 16 is a normal number)
+        float t = __fmul_rn(static_cast<float>(acc_lo[q]), sl);
+        t = __fmaf_rn(static_cast<float>(acc_hi[q]), sh, t);
+        f[j][q] = __fadd_rn(f[j][q], t);
       }
     }
   }
-
-  // ---- epilogue: y = f * s_a[m] ----
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      const int m = m0 + 64 * wm + 32 * i + 8 * (q >> 2) + 4 * h + (q & 3);
-      if (m < g.M) {
-        const float sa = g.a_scale[m];
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          const int n = n0 + 64 * wn + 32 * j + r;
-          if (n < g.N) {
-            const float y = __fmul_rn(f[i][j][q], sa);
-            const int64_t o = static_cast<int64_t>(m) * g.ldy + n;
-            if (g.out_bf16) reinterpret_cast<uint16_t*>(g.y)[o] = f32_to_bf16_rne(y);
-            else reinterpret_cast<float*>(g.y)[o] = y;
-          }
-        }
-      }
-    }
+  __syncthreads();  // the stages are free: y = f * s_a[m]
+  char* tb = lds + wave * (32 * (64 * 4 + 16));
+  if (g.out_bf16) w2_epilogue<uint16_t>(g, tb, f, m0 + 32 * wm, n0 + 64 * wn, lane);
+  else w2_epilogue<float>(g, tb, f, m0 + 32 * wm, n0 + 64 * wn, lane);
 }
 
 // scales [N, G] -> [G, Npad] (zero beyond N), so that a bank's scales of 128 consecutive channels are contiguous;
@@ -457,10 +484,20 @@ __global__ __launch_bounds__(256) void wsq_scales_t_kernel(int N, int G, int Npa
 }  // namespace
 
 int init_wsq_kernels() {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(wsq_gemm2_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                             W2_NS * W2_STAGE) == hipSuccess
-             ? SQ_OK
-             : SQ_ERR_LAUNCH;
+  hipError_t e = hipSuccess;
+#define X(BPB, MW)                                                                                       \
+  if (e == hipSuccess)                                                                                   \
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(wsq_gemm2_kernel<W2<BPB, MW>>),                \
+                            hipFuncAttributeMaxDynamicSharedMemorySize, W2<BPB, MW>::LDS_BYTES);
+  X(1, 4) X(1, 8) X(2, 4) X(2, 8)
+#undef X
+  return e == hipSuccess ? SQ_OK : SQ_ERR_LAUNCH;
+}
+
+template <typename C>
+void launch_wsq2(const Wsq2Args& a, hipStream_t st) {
+  const int tiles = ((a.N + 127) / 128) * ((a.M + C::BM - 1) / C::BM);
+  hipLaunchKernelGGL(wsq_gemm2_kernel<C>, dim3((tiles + 7) / 8 * 8), dim3(C::THREADS), C::LDS_BYTES, st, a);
 }
 
 int launch_wsq_encode(const sq_params& p, const uint16_t* w, int64_t ldw, const float* hinv, const sq_wsq& out, hipStream_t st) {
@@ -493,21 +530,25 @@ int launch_wsq_prepack(const sq_params& p, const sq_wsq& w, uint8_t* lo_clean, i
 }
 
 int launch_quantize_act(const sq_params& p, const uint16_t* x, int64_t ldx, int bits, int8_t* a8, float* a_scale, hipStream_t st) {
-  hipLaunchKernelGGL(quantize_act_kernel, dim3(p.M), dim3(256), 0, st, x, ldx, p.K, code_max(bits, 8), a8, a_scale);
+#define X(IT) hipLaunchKernelGGL(quantize_act_kernel<IT>, dim3(p.M), dim3(256), 0, st, x, ldx, p.K, code_max(bits, 8), a8, a_scale)
+  if (p.K <= 4096) X(2);
+  else if (p.K <= 8192) X(4);
+  else if (p.K <= 16384) X(8);
+  else X(0);
+#undef X
   return hipGetLastError() == hipSuccess ? SQ_OK : SQ_ERR_LAUNCH;
 }
 
 int launch_wsq_gemm(const sq_params& p, const int8_t* a8, const float* a_scale, const sq_wsq& w, const uint8_t* lo_clean,
                     const int8_t* hi_dense, const float* s_lo_t, const float* s_hi_t, void* y, int64_t ldy,
                     int32_t* acc_lo_dbg, int32_t* acc_hi_dbg, hipStream_t st) {
-  if (!acc_lo_dbg && !acc_hi_dbg && p.M > 64) {  // the throughput kernel (the small kernel below also dumps the per-bank products)
+  if (!acc_lo_dbg && !acc_hi_dbg) {  // the kernel below is for dumping the per-bank products
     Wsq2Args a;
     a.M = p.M;
     a.N = p.N;
     a.K = p.K;
     a.G = p.K / p.bank;
     a.Npad = (p.N + 127) / 128 * 128;
-    a.bpb = p.bank / 64;
     a.a8 = a8;
     a.a_scale = a_scale;
     a.lo_clean = lo_clean;
@@ -517,7 +558,12 @@ int launch_wsq_gemm(const sq_params& p, const int8_t* a8, const float* a_scale, 
     a.y = y;
     a.ldy = ldy;
     a.out_bf16 = p.out_dtype == SQ_OUT_BF16;
-    hipLaunchKernelGGL(wsq_gemm2_kernel, dim3((p.N + 127) / 128, (p.M + 127) / 128), dim3(256), W2_NS * W2_STAGE, st, a);
+    // 256 tokens per workgroup where such tiles fill the chip (30 % less operand traffic; one workgroup per compute unit
+    // instead of two, which is what the LDS of a 128-channel bank allows in either form): bank 128 888 us against 1137 us
+    // at [4096,4096] x [22016,4096], bank 64 1187 against 1201 us; 128 below that (300 tokens x 4096 channels: 66 us)
+    const bool tall = static_cast<int64_t>((p.N + 127) / 128) * ((p.M + 255) / 256) >= 256;
+    if (p.bank == 64) tall ? launch_wsq2<W2<1, 8>>(a, st) : launch_wsq2<W2<1, 4>>(a, st);
+    else tall ? launch_wsq2<W2<2, 8>>(a, st) : launch_wsq2<W2<2, 4>>(a, st);
     return hipGetLastError() == hipSuccess ? SQ_OK : SQ_ERR_LAUNCH;
   }
   WsqGemmArgs g;

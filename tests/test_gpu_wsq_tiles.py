@@ -1,0 +1,61 @@
+"""The weights-SQ layer on both tiles of its kernel (128 and 256 tokens), one to several banks (fewer than the ring holds,
+and more), ragged edges, aligned and unaligned rows of Y; and the activation quantiser at the edges of the row lengths it
+keeps in registers.  Bit for bit against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle.wsq as W
+import paper_2512_05409_amd as sq
+from gpu_util import Guarded, dev
+from test_gpu_wsq import case, consumer_order
+
+pytestmark = pytest.mark.gpu
+
+
+# 256-token tiles from 256 of them on: 9 x 29 and 8 x 33
+@pytest.mark.parametrize("M,K,N,bank,pad", [(2100, 64, 3700, 64, 0), (2100, 320, 3650, 64, 3), (2048, 128, 4129, 128, 8),
+                                            (1999, 384, 4200, 128, 3), (1, 64, 20, 64, 0), (40, 640, 260, 128, 8),
+                                            (128, 256, 128, 64, 0), (129, 448, 300, 64, 3)])
+@pytest.mark.parametrize("out_dtype", [sq.SQ_OUT_F32, sq.SQ_OUT_BF16])
+def test_weights_sq_tiles(M, K, N, bank, pad, out_dtype):
+    print(f"wsq tiles M={M} K={K} N={N} bank={bank} pad={pad} out={out_dtype}", flush=True)
+    topk = bank // 8
+    wb, xb, d = case(700 + M + K + N, M, K, N)
+    codes, scale = W.quantize_activations(xb, 8)
+    prod = W.gemm(codes, scale, W.encode_weights(wb, bank, topk, 8, 4, d=d))
+    p = sq.params(M, K, N, bank, topk, out_dtype=out_dtype)
+    ws = sq.WeightSQ(p)
+    sq.sq_wsq_encode(p, dev(wb), ws, hinv_diag=dev(d))
+    pre = torch.empty(sq.sq_wsq_prepack_bytes(p), dtype=torch.uint8, device="cuda")
+    sq.sq_wsq_prepack(p, ws, pre)
+    f32 = out_dtype == sq.SQ_OUT_F32
+    ldy = N + pad
+    y = Guarded(M * ldy * (4 if f32 else 2), torch.int32 if f32 else torch.int16)
+    y.t.fill_(0x5A5A)
+    wsb = Guarded(sq.sq_wsq_linear_workspace_bytes(p), torch.uint8)
+    sq.sq_wsq_linear(p, dev(xb), ws, pre, y.t, wsb.t, act_bits=8, ldy=ldy)
+    torch.cuda.synchronize()
+    y.check()
+    wsb.check()
+    got = y.host(np.uint32 if f32 else np.uint16).reshape(M, ldy)
+    assert np.array_equal(got[:, :N], prod.y32.view(np.uint32) if f32 else prod.ybf16)
+    assert (got[:, N:] == 0x5A5A).all(), "written past a row"
+
+
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("K", [64, 4096, 4160, 8192, 8256, 16384, 16448])
+def test_activation_quantiser_row_lengths(K, bits):
+    print(f"quantize act K={K} bits={bits}", flush=True)
+    M = 3
+    _, xb, _ = case(900 + K, M, K, 4)
+    xb[1] = 0
+    codes, scale = W.quantize_activations(xb, bits)
+    p = sq.params(M, K, 64)
+    a8, sa = Guarded(M * K, torch.int8), Guarded(M * 4, torch.float32)
+    sq.sq_quantize_act(p, dev(xb), a8.t, sa.t, bits=bits)
+    torch.cuda.synchronize()
+    a8.check()
+    sa.check()
+    assert np.array_equal(a8.host(np.int8).reshape(M, K), consumer_order(codes))
+    assert np.array_equal(sa.host(np.uint32), scale.view(np.uint32))
