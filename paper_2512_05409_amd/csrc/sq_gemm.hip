@@ -14,9 +14,15 @@
 // [evens of dword 2s | odds of dword 2s | evens of dword 2s+1 | odds of dword 2s+1].  The INT8
 // image of the high part is stored in exactly that byte order (see sq_act::hi_dense).
 //
-// Work split (the large tile): a workgroup of 4 waves computes 128 tokens x 256 output channels; a wave computes
-// 64 tokens x 128 channels for BOTH products (2 x 2x4 tiles of 32x32, 256 accumulator registers).  Smaller tiles, of
-// which a shape has at most a round, run two such groups of four waves per workgroup, each on every other K step.
+// Work split (the large tile): a workgroup of 8 waves computes 128 tokens x 256 output channels; a wave computes
+// 64 tokens x 64 channels for BOTH products (2 x 2x2 tiles of 32x32, 128 accumulator registers), so that two waves share
+// a SIMD.  That is what the matrix pipe needs: from a single wave v_mfma_i32_32x32x32_i8 issues every 21 ns, whatever
+// stands between the instructions, from two waves every 14.5 ns (measured, registers only), and up to six vector
+// instructions per matrix instruction are free then.  With 4 waves of 64 x 128 (256 accumulator registers, one wave per
+// SIMD, a quarter less LDS traffic per matrix instruction) [4096,4096] x [22016,4096] took 575 us against 526 us,
+// [2048,4096] x [12288,4096] 155 against 147 us, the single-product 256 x 256 tile 308 against 275 us.
+// Smaller tiles, of which a shape has at most a round, run two groups of four waves per workgroup, each on every other
+// K step.
 // A K step of 128 channels is copied into one of three LDS stages by LDS-direct loads, two steps
 // ahead of its use.  LDS rows are row-major with the 16-byte chunk index XOR-swizzled by the row,
 // which keeps the operand reads (32 consecutive rows per half wave) free of bank conflicts.
@@ -29,20 +35,21 @@ using namespace gemm;
 
 constexpr int KS = 128;  // channels per K step
 constexpr int kHugeMinTiles = 512;  // 256x256 tiles a single-product shape needs to use them
-constexpr int NT = 256;  // threads per workgroup
 
 // WITH_LO = false: a tile for loops without a packed low operand (the single-product modes), whose stage
 // holds no room for one; that is what lets 256 tokens x 256 channels fit three stages into LDS.
 // NS: LDS stages of the K loop.  The copy of step kt + NS - 1 is enqueued while step kt is multiplied, so a copy
 // has NS - 2 whole K steps to land before anything waits for it.
-template <int BM_, int BN_, bool WITH_LO = true, int NS_ = 3, int S_ = 1>
+template <int BM_, int BN_, int NWM_, int NWN_, bool WITH_LO = true, int S_ = 1, int NS_ = 3>
 struct Tile {
-  static constexpr int S = S_;                // K groups of four waves; group s takes the K steps s, s + S, ...
+  static constexpr int NWM = NWM_, NWN = NWN_;  // waves of a K group: NWM along the tokens, NWN along the channels
+  static constexpr int NT = 64 * NWM * NWN;   // threads of a K group
+  static constexpr int S = S_;                // K groups; group s takes the K steps s, s + S, ...
   static constexpr int NS = NS_;
   static constexpr int BM = BM_;              // tokens per workgroup
   static constexpr int BN = BN_;              // output channels per workgroup
-  static constexpr int WM = BM / 2;           // tokens per wave (waves are 2 x 2)
-  static constexpr int WN = BN / 2;           // channels per wave
+  static constexpr int WM = BM / NWM;         // tokens per wave
+  static constexpr int WN = BN / NWN;         // channels per wave
   static constexpr int TI = WM / 32;          // 32-row tiles per wave along M
   static constexpr int TJ = WN / 32;          // along N
   static constexpr int A_LO = 0;              // [BM][64 B]   packed INT4
@@ -51,6 +58,7 @@ struct Tile {
   static constexpr int STAGE = B_OFF + BN * 64;
   static constexpr int LDS_BYTES = S * NS * STAGE;
   static constexpr int THREADS = NT * S;
+  static_assert((!WITH_LO || BM * 4 % NT == 0) && BM * 8 % NT == 0 && BN * 4 % NT == 0, "whole copies per wave");
   static_assert(NS >= 3 && LDS_BYTES <= 160 * 1024, "stages must fit in the 160 KB of LDS");
   static_assert((S - 1) * BM * BN * 8 <= LDS_BYTES, "the other groups' partial sums must fit, too");
 };
@@ -81,9 +89,9 @@ __device__ __forceinline__ void pipeline_barrier() {
 // chunk p ^ swizzle(row).  Four (or eight) consecutive lanes still read 64 (128) contiguous bytes.
 template <typename T, bool LO, bool HI>
 struct Pipe {
-  static constexpr int N_LO = LO ? T::BM * 4 / NT : 0;
-  static constexpr int N_HI = HI ? T::BM * 8 / NT : 0;
-  static constexpr int N_B = T::BN * 4 / NT;
+  static constexpr int N_LO = LO ? T::BM * 4 / T::NT : 0;
+  static constexpr int N_HI = HI ? T::BM * 8 / T::NT : 0;
+  static constexpr int N_B = T::BN * 4 / T::NT;
   static constexpr int NLOAD = N_LO + N_HI + N_B;  // loads per wave per K step
 
   const char* p_lo[N_LO > 0 ? N_LO : 1];  // per-lane source of each load at k = 0
@@ -98,10 +106,10 @@ struct Pipe {
 
   __device__ __forceinline__ void init(const uint8_t* a_lo, int64_t lda_lo, const int8_t* a_hi, int64_t lda_hi,
                                        const uint8_t* b, int64_t ldb, int kext_, int m0, int n0, int M, int N, int rot8) {
-    const int tid = threadIdx.x & (NT - 1);
+    const int tid = threadIdx.x & (T::NT - 1);
     kext = kext_;
     wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    grp = T::S == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / NT);
+    grp = T::S == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / T::NT);
     steps = (kext + KS * T::S - 1) / (KS * T::S);
     // With two K groups (few tiles: operands come from far, little is shared) every XCD starts at its own place of K, so
     // that rows 4 KB apart are not asked for at the same few hundred bytes by the whole chip at a time.  Only the last
@@ -117,17 +125,17 @@ struct Pipe {
     }
 #pragma unroll
     for (int i = 0; i < N_LO; ++i) {
-      const int m = min(m0 + ((tid + NT * i) >> 2), M - 1);
+      const int m = min(m0 + ((tid + T::NT * i) >> 2), M - 1);
       p_lo[i] = reinterpret_cast<const char*>(a_lo) + m * lda_lo + (kc_lo >> 1);
     }
 #pragma unroll
     for (int i = 0; i < N_HI; ++i) {
-      const int m = min(m0 + ((tid + NT * i) >> 3), M - 1);
+      const int m = min(m0 + ((tid + T::NT * i) >> 3), M - 1);
       p_hi[i] = reinterpret_cast<const char*>(a_hi) + m * lda_hi + kc_hi;
     }
 #pragma unroll
     for (int i = 0; i < N_B; ++i) {
-      const int n = min(n0 + ((tid + NT * i) >> 2), N - 1);
+      const int n = min(n0 + ((tid + T::NT * i) >> 2), N - 1);
       p_b[i] = reinterpret_cast<const char*>(b) + n * ldb + (kc_lo >> 1);
     }
   }
@@ -148,17 +156,17 @@ struct Pipe {
 #pragma unroll
     for (int i = 0; i < N_LO; ++i) {
       const char* src = lo_ok ? p_lo[i] + (k0 >> 1) : zero;
-      __builtin_amdgcn_global_load_lds(src, (lds_ptr_t)(stage + T::A_LO + (NT * i + 64 * wave) * 16), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds(src, (lds_ptr_t)(stage + T::A_LO + (T::NT * i + 64 * wave) * 16), 16, 0, 0);
     }
 #pragma unroll
     for (int i = 0; i < N_HI; ++i) {
       const char* src = hi_ok ? p_hi[i] + k0 : zero;
-      __builtin_amdgcn_global_load_lds(src, (lds_ptr_t)(stage + T::A_HI + (NT * i + 64 * wave) * 16), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds(src, (lds_ptr_t)(stage + T::A_HI + (T::NT * i + 64 * wave) * 16), 16, 0, 0);
     }
 #pragma unroll
     for (int i = 0; i < N_B; ++i) {
       const char* src = lo_ok ? p_b[i] + (k0 >> 1) : zero;
-      __builtin_amdgcn_global_load_lds(src, (lds_ptr_t)(stage + T::B_OFF + (NT * i + 64 * wave) * 16), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds(src, (lds_ptr_t)(stage + T::B_OFF + (T::NT * i + 64 * wave) * 16), 16, 0, 0);
     }
   }
 };
@@ -373,7 +381,7 @@ struct EpiScales {
 
 template <typename T>
 __device__ __forceinline__ void load_epi_scales(EpiScales<T>& e, const GemmArgs& g, int m0, int n0, int wn, int lane) {
-  const int tid = threadIdx.x & (NT - 1);
+  const int tid = threadIdx.x & (T::NT - 1);
   const int m = min(m0 + (tid < T::BM ? tid : 0), g.M - 1);
   e.slo = g.s_lo ? g.s_lo[m] : 0.0f;
   e.shi = g.s_hi[m];
@@ -394,8 +402,8 @@ __device__ __forceinline__ void epilogue_typed(const GemmArgs& g, const EpiScale
   constexpr int CHUNKS = T::WN / PER16;   // 16-byte chunks per row
   constexpr int ROWS_PER_PASS = 64 / CHUNKS;
   constexpr int SC_BYTES = 2 * T::BM * 4;  // [0, BM): s_lo, [BM, 2 BM): s_hi
-  static_assert(SC_BYTES + 4 * 32 * ROW <= T::LDS_BYTES, "transposition buffers must fit in the stage memory");
-  const int tid = threadIdx.x & (NT - 1);
+  static_assert(SC_BYTES + T::NT / 64 * 32 * ROW <= T::LDS_BYTES, "transposition buffers must fit in the stage memory");
+  const int tid = threadIdx.x & (T::NT - 1);
   float* sc = reinterpret_cast<float*>(lds);
   char* tb = lds + SC_BYTES + wave * (32 * ROW);
   if (tid < T::BM) {
@@ -487,7 +495,7 @@ __device__ __forceinline__ void join_groups(char* lds, int grp, int wave, int la
                                             v16i (&acc_hi)[T::TI][T::TJ]) {
   constexpr int PER_WAVE = T::TI * T::TJ * 8 * 1024;  // two products, 16 registers of 64 lanes
   auto at = [&](int g, int i, int j, int p, int q) {
-    return reinterpret_cast<v4i*>(lds + ((g - 1) * 4 + wave) * PER_WAVE + (((i * T::TJ + j) * 2 + p) * 4 + q) * 1024 + lane * 16);
+    return reinterpret_cast<v4i*>(lds + ((g - 1) * (T::NT / 64) + wave) * PER_WAVE + (((i * T::TJ + j) * 2 + p) * 4 + q) * 1024 + lane * 16);
   };
   if (grp != 0) {
 #pragma unroll
@@ -526,11 +534,11 @@ __device__ __forceinline__ void join_groups(char* lds, int grp, int wave, int la
 template <typename T, int MODE>
 __global__ __launch_bounds__(T::THREADS) void gemm_kernel(GemmArgs g) {
   extern __shared__ __attribute__((aligned(16))) char lds_all[];
-  const int tid = threadIdx.x & (NT - 1);
-  const int grp = T::S == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / NT);
+  const int tid = threadIdx.x & (T::NT - 1);
+  const int grp = T::S == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / T::NT);
   const int lane = tid & 63, wave = tid >> 6;
   char* lds = lds_all + grp * (T::NS * T::STAGE);  // every K group has its own stages
-  const int wm = wave >> 1, wn = wave & 1;
+  const int wm = wave / T::NWN, wn = wave % T::NWN;
   int tm, tn;
   tile_of_block(blockIdx.x, (g.M + T::BM - 1) / T::BM, (g.N + T::BN - 1) / T::BN, tm, tn);
   if (tm < 0) return;
@@ -597,19 +605,18 @@ int launch_mode(const GemmArgs& g, hipStream_t st) {
 
 // Three stages everywhere: a fourth stage for the 128x256 tile (exactly the 160 KB of LDS) was timed and changes
 // nothing (c3: 680 us either way on dense random operands) -- the copies are not what the loop waits for.
-typedef Tile<128, 256> Big;                  // matrix-core bound shapes
-typedef Tile<128, 128> Mid;                  // too few of those to occupy every compute unit
-typedef Tile<64, 128, true, 3, 2> SmallWide;  // fewer still: two K groups of four waves per workgroup, so that a compute
-typedef Tile<64, 64, true, 3, 2> Small;       // unit has two waves per SIMD although it has one workgroup
-typedef Tile<256, 256, false> Huge;  // single-product modes on large shapes: with one accumulator set a wave
-                                     // holds 128 x 128 outputs, which halves the operand traffic and the
-                                     // widening arithmetic per matrix instruction and doubles the matrix
-                                     // instructions between two barriers to 64, as in the two-product loop
+typedef Tile<128, 256, 2, 4> Big;                  // matrix-core bound shapes
+typedef Tile<128, 128, 4, 2> Mid;                  // too few of those to occupy every compute unit
+typedef Tile<64, 128, 2, 2, true, 2> SmallWide;  // fewer still: two K groups of four waves per workgroup, so that a compute
+typedef Tile<64, 64, 2, 2, true, 2> Small;       // unit has two waves per SIMD although it has one workgroup
+typedef Tile<256, 256, 2, 4, false> Huge;  // single-product modes on large shapes: with one accumulator set a wave
+                                           // holds 128 x 64 outputs, which halves the operand traffic and the
+                                           // widening arithmetic per matrix instruction
 
 enum Variant { V_HUGE, V_BIG, V_MID, V_SMALL_WIDE, V_SMALL, V_FEW };
 
 // Which kernel a shape runs on.  Every tile kernel fills a compute unit with one workgroup, so a launch takes
-// ceil(tiles / 256) rounds, and a round of each tile its own time: at K = 4096, two products, 48 us (Big), 28.5 us
+// ceil(tiles / 256) rounds, and a round of each tile its own time: at K = 4096, two products, 48 us (Big), 27 us
 // (Mid), 18 us (SmallWide), 11.5 us (Small); single product 35 / 19 / 13.5 / 9 us.  The least rounds x time wins, a
 // larger tile on near ties (it moves less data).  Measured against the old rule (Big above 128 of its tiles, else Mid;
 // 64x64 up to 64 tokens): [333,11008] x [4095,11008] 66.9 -> 42.2 us (SmallWide), [128,4096] x [12288,4096] 26.7 ->
@@ -619,7 +626,7 @@ Variant pick_variant(int M, int N, bool single) {
   auto tiles = [&](int bm, int bn) { return static_cast<int64_t>((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
   if (single && tiles(256, 256) >= kHugeMinTiles) return V_HUGE;
   struct { Variant v; int bm, bn, two, one; } const t[] = {
-      {V_BIG, 128, 256, 480, 350}, {V_MID, 128, 128, 285, 190}, {V_SMALL_WIDE, 64, 128, 180, 135}, {V_SMALL, 64, 64, 115, 90}};
+      {V_BIG, 128, 256, 460, 320}, {V_MID, 128, 128, 270, 185}, {V_SMALL_WIDE, 64, 128, 180, 135}, {V_SMALL, 64, 64, 115, 90}};
   Variant best = V_BIG;
   int64_t least = INT64_MAX;
   for (const auto& c : t) {
