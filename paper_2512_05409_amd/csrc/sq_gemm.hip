@@ -213,7 +213,8 @@ __device__ __forceinline__ void widen_slice(Wide<T>& w, const Frags<T>& f, int s
   }
 }
 
-// The matrix instructions of one 32-channel slice (s = 0/1): 2 * TI * TJ of them, all independent.
+// The matrix instructions of one 32-channel slice (s = 0/1): 2 * TI * TJ of them, all independent.  The weights are the
+// row operand: a lane then holds the outputs of one token, four consecutive channels at a time.
 template <typename T, bool LO, bool HI>
 __device__ __forceinline__ void mma_slice(const Wide<T>& w, const Frags<T>& f, int s, v16i (&acc_lo)[T::TI][T::TJ],
                                           v16i (&acc_hi)[T::TI][T::TJ]) {
@@ -221,8 +222,8 @@ __device__ __forceinline__ void mma_slice(const Wide<T>& w, const Frags<T>& f, i
   for (int i = 0; i < T::TI; ++i) {
 #pragma unroll
     for (int j = 0; j < T::TJ; ++j) {
-      if (LO) acc_lo[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(w.alo[i], w.bw[j], acc_lo[i][j], 0, 0, 0);
-      if (HI) acc_hi[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(f.ahi[i][s], w.bw[j], acc_hi[i][j], 0, 0, 0);
+      if (LO) acc_lo[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(w.bw[j], w.alo[i], acc_lo[i][j], 0, 0, 0);
+      if (HI) acc_hi[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(w.bw[j], f.ahi[i][s], acc_hi[i][j], 0, 0, 0);
     }
   }
 }
@@ -367,29 +368,29 @@ __device__ __forceinline__ void wave_lds_fence() {
 }
 
 // Epilogue: Y = (acc_lo * s_lo[m] + acc_hi * s_hi[m]) * s_w[n], in this order, in fp32.
-// Accumulator register r of lane l of a 32x32 tile is row 8*(r/4) + 4*(l/32) + r%4, column l%32, so a
-// lane holds single elements of many rows.  The per-token scales of the workgroup's rows and the
-// finished outputs go through LDS (free after the K loops): every wave transposes 32 rows x WN columns
-// at a time and then stores 16 bytes per lane, whole row segments at once.
+// Accumulator register r of lane l of a 32x32 tile is channel 8*(r/4) + 4*(l/32) + r%4 of token l%32.  The finished
+// outputs go through LDS (free after the K loops), four channels at a time: every wave transposes 32 tokens x WN channels
+// and then stores 16 bytes per lane, whole row segments at once.  (With the tokens as rows a lane held single elements
+// of many rows and wrote them to LDS 2 bytes at a time: [4096,4096] x [22016,4096] 552 -> 540 us, the single-product
+// kernel 282 -> 264 us.)
 // The scales a thread contributes to the epilogue, fetched at the start of the kernel so that their
 // latency hides under the K loop.
 template <typename T>
 struct EpiScales {
-  float slo, shi;    // thread t < BM: s_lo and s_hi of row m0 + t
-  float sw[T::TJ];   // s_w of this lane's column in each of the wave's 32-column tiles
+  float slo[T::TI], shi[T::TI];  // s_lo and s_hi of this lane's token in each of the wave's 32-token tiles
+  float sw;                      // thread t < BN: s_w of channel n0 + t
 };
 
 template <typename T>
-__device__ __forceinline__ void load_epi_scales(EpiScales<T>& e, const GemmArgs& g, int m0, int n0, int wn, int lane) {
+__device__ __forceinline__ void load_epi_scales(EpiScales<T>& e, const GemmArgs& g, int m0, int n0, int wm, int lane) {
   const int tid = threadIdx.x & (T::NT - 1);
-  const int m = min(m0 + (tid < T::BM ? tid : 0), g.M - 1);
-  e.slo = g.s_lo ? g.s_lo[m] : 0.0f;
-  e.shi = g.s_hi[m];
 #pragma unroll
-  for (int j = 0; j < T::TJ; ++j) {
-    const int n = n0 + wn * T::WN + j * 32 + (lane & 31);
-    e.sw[j] = g.s_w[min(n, g.N - 1)];
+  for (int i = 0; i < T::TI; ++i) {
+    const int m = min(m0 + wm * T::WM + i * 32 + (lane & 31), g.M - 1);
+    e.slo[i] = g.s_lo ? g.s_lo[m] : 0.0f;
+    e.shi[i] = g.s_hi[m];
   }
+  e.sw = g.s_w[min(n0 + (tid < T::BN ? tid : 0), g.N - 1)];
 }
 
 template <typename T, typename OutT>
@@ -401,15 +402,13 @@ __device__ __forceinline__ void epilogue_typed(const GemmArgs& g, const EpiScale
   constexpr int PER16 = 16 / ESZ;         // outputs per 16-byte store
   constexpr int CHUNKS = T::WN / PER16;   // 16-byte chunks per row
   constexpr int ROWS_PER_PASS = 64 / CHUNKS;
-  constexpr int SC_BYTES = 2 * T::BM * 4;  // [0, BM): s_lo, [BM, 2 BM): s_hi
+  constexpr int SC_BYTES = T::BN * 4;     // s_w
+  static_assert(T::BN <= T::NT, "one scale per thread");
   static_assert(SC_BYTES + T::NT / 64 * 32 * ROW <= T::LDS_BYTES, "transposition buffers must fit in the stage memory");
   const int tid = threadIdx.x & (T::NT - 1);
   float* sc = reinterpret_cast<float*>(lds);
   char* tb = lds + SC_BYTES + wave * (32 * ROW);
-  if (tid < T::BM) {
-    sc[tid] = es.slo;
-    sc[T::BM + tid] = es.shi;
-  }
+  if (tid < T::BN) sc[tid] = es.sw;
   // workgroup barrier without the memory fence of __syncthreads(): only LDS traffic has to be ordered here
   pipeline_barrier<63>();
   const bool vec_ok = (g.ldy % PER16) == 0;  // rows of Y stay 16-byte aligned
@@ -417,26 +416,27 @@ __device__ __forceinline__ void epilogue_typed(const GemmArgs& g, const EpiScale
 #pragma unroll
   for (int i = 0; i < T::TI; ++i) {
 #pragma unroll
-    for (int rq = 0; rq < 4; ++rq) {
-      const int rl0 = 8 * rq + 4 * (lane >> 5);  // 4 consecutive rows of the 32: registers 4 rq + e
-      // (clang vector types, not HIP's float4: the compiler orders reads of the latter after every LDS-direct
-      // load in flight with a full vmcnt(0) wait)
-      const f32x4 slo4 = *reinterpret_cast<const f32x4*>(sc + wm * T::WM + i * 32 + rl0);
-      const f32x4 shi4 = *reinterpret_cast<const f32x4*>(sc + T::BM + wm * T::WM + i * 32 + rl0);
-      const float slo[4] = {slo4[0], slo4[1], slo4[2], slo4[3]};
-      const float shi[4] = {shi4[0], shi4[1], shi4[2], shi4[3]};
+    for (int j = 0; j < T::TJ; ++j) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
+      for (int rq = 0; rq < 4; ++rq) {
+        const int c0 = j * 32 + 8 * rq + 4 * (lane >> 5);  // 4 consecutive channels of the wave's: registers 4 rq + e
+        // (clang vector types, not HIP's float4: the compiler orders reads of the latter after every LDS-direct
+        // load in flight with a full vmcnt(0) wait)
+        const f32x4 sw = *reinterpret_cast<const f32x4*>(sc + wn * T::WN + c0);
+        f32x4 y;
 #pragma unroll
-        for (int j = 0; j < T::TJ; ++j) {
+        for (int e = 0; e < 4; ++e) {
           // the accumulators carry the widening factors 256 and 16: shifted out exactly, as integers
-          float t = __fmul_rn(static_cast<float>(acc_lo[i][j][4 * rq + e] >> 8), slo[e]);
-          t = __fmaf_rn(static_cast<float>(acc_hi[i][j][4 * rq + e] >> 4), shi[e], t);
-          const float y = __fmul_rn(t, es.sw[j]);
-          OutT* dst = reinterpret_cast<OutT*>(tb + (rl0 + e) * ROW) + j * 32 + (lane & 31);
-          if constexpr (ESZ == 2) *dst = bf16_rne(y);
-          else *dst = y;
+          float t = __fmul_rn(static_cast<float>(acc_lo[i][j][4 * rq + e] >> 8), es.slo[i]);
+          t = __fmaf_rn(static_cast<float>(acc_hi[i][j][4 * rq + e] >> 4), es.shi[i], t);
+          y[e] = __fmul_rn(t, sw[e]);
         }
+        char* dst = tb + (lane & 31) * ROW + c0 * ESZ;
+        if constexpr (ESZ == 2)
+          *reinterpret_cast<v2u*>(dst) = v2u{bf16_rne(y[0]) | static_cast<unsigned>(bf16_rne(y[1])) << 16,
+                                             bf16_rne(y[2]) | static_cast<unsigned>(bf16_rne(y[3])) << 16};
+        else
+          *reinterpret_cast<f32x4*>(dst) = y;
       }
     }
     wave_lds_fence();  // the buffer is private to the wave: its LDS operations execute in order
@@ -468,8 +468,8 @@ __device__ __forceinline__ void epilogue_typed(const GemmArgs& g, const EpiScale
       for (int j = 0; j < T::TJ; ++j)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const int m = m0 + wm * T::WM + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-          const int n = n0 + wn * T::WN + j * 32 + (lane & 31);
+          const int m = m0 + wm * T::WM + i * 32 + (lane & 31);
+          const int n = n0 + wn * T::WN + j * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
           if (m < g.M && n < g.N) {
             if (g.acc_lo_dbg) g.acc_lo_dbg[static_cast<int64_t>(m) * g.N + n] = acc_lo[i][j][r] >> 8;
             if (g.acc_hi_dbg) g.acc_hi_dbg[static_cast<int64_t>(m) * g.N + n] = acc_hi[i][j][r] >> 4;
@@ -547,7 +547,7 @@ __global__ __launch_bounds__(T::THREADS) void gemm_kernel(GemmArgs g) {
   // Order: scales first (they are the oldest vector-memory operations, so no later wait is held up by
   // them), then the first copies of the K loop, then the accumulators are cleared under their latency.
   EpiScales<T> es;
-  load_epi_scales<T>(es, g, m0, n0, wn, lane);
+  load_epi_scales<T>(es, g, m0, n0, wm, lane);
   constexpr bool HI1 = MODE == 0;  // the first loop also carries the INT8 operand (dynamic mode)
   Pipe<T, true, HI1> p1;           // MODE 0: low + zero-padded high; MODE 1: low only; MODE 2: unused
   Pipe<T, false, true> p2;         // MODE 1, 2: the compact high loop
