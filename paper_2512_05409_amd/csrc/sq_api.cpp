@@ -232,6 +232,8 @@ int sq_encode(const sq_params* p, const uint16_t* x_bf16, int64_t ldx, const uin
   rc = check_act(p, out);
   if (rc != SQ_OK) return rc;
   if ((rc = sq::ensure_device_ready()) != SQ_OK) return rc;
+  if (p->mode == SQ_DYNAMIC_TIED && sq::encode_few_supports(*p))
+    return sq::launch_encode_few(*p, x_bf16, ldx, *out, true, static_cast<hipStream_t>(stream));
   if (p->mode == SQ_DYNAMIC_TIED)
     return sq::launch_encode_stream(*p, x_bf16, ldx, *out, out->hi_dense, true, 127.0f, 7.0f, static_cast<hipStream_t>(stream));  // (8/4) only
   return sq::launch_encode_dynamic(*p, x_bf16, ldx, *out, static_cast<hipStream_t>(stream));

@@ -33,6 +33,9 @@ bool encode_stream_supports(const sq_params& p);
 int init_encode_stream_kernels();
 int launch_encode_stream(const sq_params& p, const uint16_t* x, int64_t ldx, const sq_act& out, int8_t* image, bool tied,
                          float q_hi, float q_lo, hipStream_t st);
+// Few banks, several lanes per bank (sq_encode_few.hip).
+bool encode_few_supports(const sq_params& p);
+int launch_encode_few(const sq_params& p, const uint16_t* x, int64_t ldx, const sq_act& out, bool tied, hipStream_t st);
 // Row-staged static encoder (sq_encode_static.hip): shapes it takes, one-time initialisation, launcher.
 bool encode_static_gather_supports(const sq_params& p);
 int init_encode_static_kernels();

@@ -453,6 +453,7 @@ int init_encode_kernels() {
 }
 
 int launch_encode_dynamic(const sq_params& p, const uint16_t* x, int64_t ldx, const sq_act& out, hipStream_t st) {
+  if (encode_few_supports(p)) return launch_encode_few(p, x, ldx, out, false, st);
   // Rows whose bank count is a power of two up to 64, or 64 / 128 / 256, take the streaming kernel; the
   // kernel below covers every other K / bank <= 512 (checked by the caller).
   if (encode_stream_supports(p))
