@@ -558,10 +558,17 @@ int launch_wsq_gemm(const sq_params& p, const int8_t* a8, const float* a_scale, 
     a.y = y;
     a.ldy = ldy;
     a.out_bf16 = p.out_dtype == SQ_OUT_BF16;
-    // 256 tokens per workgroup where such tiles fill the chip (30 % less operand traffic; one workgroup per compute unit
-    // instead of two, which is what the LDS of a 128-channel bank allows in either form): bank 128 888 us against 1137 us
-    // at [4096,4096] x [22016,4096], bank 64 1187 against 1201 us; 128 below that (300 tokens x 4096 channels: 66 us)
-    const bool tall = static_cast<int64_t>((p.N + 127) / 128) * ((p.M + 255) / 256) >= 256;
+    // 256 tokens per workgroup (30 % less operand traffic) or 128, by the rounds that the 256 compute units make.  A tile
+    // of 256 tokens takes a compute unit alone.  Banks of 64: two of the 128-token tiles share one, do the same work in
+    // about 1.02 of the time and leave no half-empty last round, so the tall tile is taken where its rounds are 15/16
+    // full: 1207 against 1223 us at [4096,4096] x [22016,4096] (2752 tall tiles), but 103 against 59 us and so 128 tokens
+    // at [600,2048] x [11008,2048] (258 tall tiles).  Banks of 128: the LDS holds one workgroup of either form, and a tall
+    // round takes 1.57 short ones, less where the last is light: the tall tile up to two of its rounds for three short
+    // ones.  871 against 1123 us at [4096,4096] x [22016,4096], 42 against 53 us at [1024,2048] x [5120,2048] (one round
+    // for two), but 147 against 112 us and so 128 tokens at [1100,4096] x [6912,4096] (two rounds in either form).
+    const int64_t cols = (p.N + 127) / 128, short_tiles = cols * ((p.M + 127) / 128);
+    const int64_t tall_rounds = (cols * ((p.M + 255) / 256) + 255) / 256;
+    const bool tall = p.bank == 64 ? 480 * tall_rounds <= short_tiles : 3 * tall_rounds <= 2 * ((short_tiles + 255) / 256);
     if (p.bank == 64) tall ? launch_wsq2<W2<1, 8>>(a, st) : launch_wsq2<W2<1, 4>>(a, st);
     else tall ? launch_wsq2<W2<2, 8>>(a, st) : launch_wsq2<W2<2, 4>>(a, st);
     return hipGetLastError() == hipSuccess ? SQ_OK : SQ_ERR_LAUNCH;
