@@ -120,9 +120,10 @@ typedef struct {
  * The format at its equivalent bit width (Section 4.1: y = (1-s)*h_high + s*h_low bits per element): per token
  * row a bit stream of K*y/8 bytes = the high codes of the high channels at h_high bits each, then the low codes
  * of the LOW channels only at h_low bits each, ascending channel order; code t of a section occupies its bits
- * [t*h, (t+1)*h), bit i of a section is bit i%8 of its byte i/8, two's complement.  The mask and the scales of
- * the sq_act are stored beside it, unchanged.
- *   sq_storage_row_bytes: K*y/8 (0 for invalid parameters)
+ * [t*h, (t+1)*h), bit i of a section is bit i%8 of its byte i/8, two's complement.  A low section that is not
+ * whole bytes (h_low = 3 with a number of high channels that is no multiple of 8) ends in four zero bits.  The mask
+ * and the scales of the sq_act are stored beside it, unchanged.
+ *   sq_storage_row_bytes: K*y/8, rounded up (0 for invalid parameters)
  *   sq_pack_storage:   a (d_lo, hi_val, mask as in sq_gemm)  ->  packed device [M, sq_storage_row_bytes(p)]
  *   sq_unpack_storage: packed, a->mask  ->  a->d_lo, a->hi_val   (the exact inverse)
  * Storage conversions, not part of the layer's hot path; they only enqueue work on `stream`.

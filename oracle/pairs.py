@@ -17,7 +17,8 @@ pack_storage / unpack_storage: the format at its equivalent bit width.  Reading 
 not a layout): per token row, the high codes of the high channels at h_high bits each, then the low codes of
 the LOW channels only at h_low bits each, both in ascending channel order, as one little-endian bit stream per
 section (code t occupies bits [t*h, (t+1)*h) of its section; bit i of a section is bit i%8 of its byte i/8;
-h-bit two's complement).  Row size = K * y / 8 bytes exactly; the mask and the two scales are stored beside it.
+h-bit two's complement).  Row size = K * y / 8 bytes; a low section that is not whole bytes (h_low = 3, a number of high
+channels that is no multiple of 8) is padded to them with zero bits.  The mask and the two scales are stored beside it.
 
 pack_storage_sentinel / unpack_storage_sentinel: the implicit-mask form of Section 3.1 / Section 3.2.1 ("the unused
 largest value of the low-precision format is considered as a high-precision mask"): the low section covers ALL K
@@ -82,7 +83,7 @@ def encode_pair(x_bits: np.ndarray, bank: int, topk: int, h_high: int, h_low: in
 
 def storage_row_bytes(K: int, bank: int, topk: int, h_high: int, h_low: int) -> int:
     k_hi = K // bank * topk
-    return (k_hi * h_high + (K - k_hi) * h_low) // 8
+    return k_hi * h_high // 8 + ((K - k_hi) * h_low + 7) // 8
 
 
 def _flags(enc: Encoded) -> np.ndarray:
@@ -100,7 +101,7 @@ def _low_codes(enc: Encoded) -> np.ndarray:
 
 
 def _pack_section(codes: np.ndarray, h: int) -> np.ndarray:
-    """[n] integer codes -> little-endian bit stream of n*h bits (n*h a multiple of 8)."""
+    """[n] integer codes -> little-endian bit stream of n*h bits, padded to whole bytes with zeros."""
     u = (codes.astype(np.int64) & ((1 << h) - 1)).astype(np.uint8)
     bits = ((u[:, None] >> np.arange(h, dtype=np.uint8)[None, :]) & 1).reshape(-1)
     return np.packbits(bits, bitorder="little")

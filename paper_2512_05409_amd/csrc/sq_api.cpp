@@ -346,7 +346,7 @@ int sq_linear(const sq_params* p, const uint16_t* x_bf16, int64_t ldx, const uin
 size_t sq_storage_row_bytes(const sq_params* p) {
   if (check_params(p) != SQ_OK) return 0;
   const int hh = p->h_high ? p->h_high : 8, hl = p->h_low ? p->h_low : 4;
-  return static_cast<size_t>(k_hi_of(p)) * hh / 8 + static_cast<size_t>(p->K - k_hi_of(p)) * hl / 8;
+  return static_cast<size_t>(k_hi_of(p)) * hh / 8 + (static_cast<size_t>(p->K - k_hi_of(p)) * hl + 7) / 8;
 }
 
 size_t sq_storage_row_bytes_sentinel(const sq_params* p) {

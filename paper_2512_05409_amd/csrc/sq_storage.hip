@@ -215,7 +215,7 @@ int launch_storage(const sq_params& p, const sq_act& act, uint8_t* packed, bool 
   a.hl = p.h_low ? p.h_low : 4;
   a.K_hi = p.K / p.bank * p.topk;  // a multiple of 4 for every format
   a.hi_bytes = a.K_hi * a.hh / 8;
-  a.row_bytes = a.hi_bytes + (sentinel ? p.K : p.K - a.K_hi) * a.hl / 8;
+  a.row_bytes = a.hi_bytes + ((sentinel ? p.K : p.K - a.K_hi) * a.hl + 7) / 8;  // (8/3) may end in half a byte, padded with zeros
   a.mask_out = act.mask;
   a.mask_stride = p.mode == SQ_STATIC ? 0 : p.K / 32;
   a.mask = act.mask;

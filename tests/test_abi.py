@@ -33,6 +33,18 @@ def test_every_declared_symbol_is_exported(L):
         assert getattr(L, n) is not None
 
 
+def test_storage_row_holds_every_bit(L):
+    """Every bit of the two sections has a place in the row, also where the low section is not whole bytes."""
+    for K in range(64, 1344, 64):
+        for bank, topk in [(32, 2), (32, 4), (64, 4), (64, 8), (128, 8)]:
+            for hh, hl in [(8, 4), (8, 3), (8, 2), (4, 2)]:
+                if K % bank == 0:
+                    k_hi = K // bank * topk
+                    p = sq.params(16, K, 64, bank, topk, h_high=hh, h_low=hl)
+                    assert sq.sq_storage_row_bytes(p) == -(-(k_hi * hh + (K - k_hi) * hl) // 8), (K, bank, topk, hh, hl)
+                    assert sq.sq_storage_row_bytes_sentinel(p) == (k_hi * hh + K * hl) // 8
+
+
 def test_status_strings(L):
     assert sq.status_string(0) == "SQ_OK"
     for code in range(-8, 0):

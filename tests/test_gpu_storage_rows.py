@@ -14,7 +14,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("h_high,h_low", [(8, 4), (8, 3), (4, 2)])
 @pytest.mark.parametrize("M,K,bank,topk", [(1, 64, 64, 8), (130, 64, 32, 8), (37, 512, 64, 16), (5, 8128, 64, 32),
-                                           (3, 8192, 128, 8), (2, 16384, 32, 2), (2, 65536, 128, 32)])
+                                           (3, 8192, 128, 8), (2, 16384, 32, 2), (2, 65536, 128, 32),
+                                           (33, 576, 64, 4), (7, 320, 32, 2)])  # (8/3): low sections that end in half a byte
 @pytest.mark.parametrize("form,offset", [("dynamic", 0), ("dynamic", 13), ("static", 3), ("sentinel", 0), ("sentinel", 6)])
 def test_storage_rows(M, K, bank, topk, h_high, h_low, form, offset):
     if form == "static" and (K // bank * topk) % 32:

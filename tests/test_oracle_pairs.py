@@ -113,6 +113,23 @@ def test_pack_by_hand_and_round_trip():
         assert np.array_equal(back.d_lo, enc.d_lo) and np.array_equal(back.hi_val, enc.hi_val)
 
 
+def test_low_section_that_ends_in_half_a_byte():
+    # K = 192 with four high channels per bank of 64: 12 high bytes, then 180 codes of 3 bits = 67.5 bytes, stored as 68.
+    # The last three codes 1, -1, 3 (001, 111, 011) are bits 531 ... 539 of the section: byte 66 holds 1 0 0 1 1 from its bit 3
+    # on, byte 67 the rest, 1 1 1 0, and four zero bits
+    x = np.zeros((1, 3, 64), np.float32)
+    x[0, :, :4] = 127
+    x = x.reshape(1, 192)
+    x[0, -3:] = 1, -1, 3
+    enc = oracle.encode_pair(f32_to_bf16_bits(x), 64, 4, 8, 3)
+    assert list(unpack_int4(enc.d_lo)[0, -3:]) == [1, -1, 3]
+    p = oracle.pack_storage(enc, 8, 3)
+    assert p.shape == (1, 12 + 68) and oracle.storage_row_bytes(192, 64, 4, 8, 3) == 80
+    assert [int(v) for v in p[0, -2:]] == [0b11001000, 0b0111]
+    back = oracle.unpack_storage(p, enc.mask, 192, 64, 4, 8, 3, enc.s_lo, enc.s_hi)
+    assert np.array_equal(back.d_lo, enc.d_lo) and np.array_equal(back.hi_val, enc.hi_val)
+
+
 def test_sentinel_form_by_hand_and_round_trip():
     # (8/2), one bank of 32 inside K = 64 (k = 4): low codes are -1, 0, 1; the high channels carry v_mask = -2
     # (bit pattern 10).  Channels 0..3 high; low codes of channels 4.. : 1, -1, 0, 1 -> 2-bit patterns 01, 11, 00, 01.
@@ -145,7 +162,7 @@ MUTANTS = [
     ("round half up (high)", "h = np.clip(np.rint((x[m] * inv_hi).astype(F32)), -q_hi, q_hi)", "h = np.clip(np.floor((x[m] * inv_hi).astype(F32) + F32(0.5)), -q_hi, q_hi)"),
     ("low codes kept at high channels", "        d[is_hi] = 0\n", ""),
     ("bit stream is MSB first", 'return np.packbits(bits, bitorder="little")', 'return np.packbits(bits, bitorder="big")'),
-    ("storage counts the low part over all channels", "return (k_hi * h_high + (K - k_hi) * h_low) // 8", "return (k_hi * h_high + K * h_low) // 8"),
+    ("storage counts the low part over all channels", "((K - k_hi) * h_low + 7) // 8", "(K * h_low + 7) // 8"),
     ("sentinel is the largest positive code", "v_mask = -(1 << (h_low - 1))\n    out = np.zeros", "v_mask = (1 << (h_low - 1)) - 1\n    out = np.zeros"),
     ("sentinel form keeps the low codes at the high channels", "ls = _pack_section(np.where(flags[m], v_mask, d[m]), h_low)", "ls = _pack_section(d[m], h_low)"),
     ("low section packs the high channels too", "ls = _pack_section(d[m][~flags[m]], h_low)", "ls = _pack_section(d[m], h_low)[: out.shape[1] - len(hs)]"),
