@@ -207,12 +207,11 @@ int sq_encode(const sq_params *p, const uint16_t *x_bf16, int64_t ldx, const uin
 int sq_gemm(const sq_params *p, const sq_act *a, const sq_weight *w, void *y, int64_t ldy,
             int32_t *acc_lo_dbg, int32_t *acc_hi_dbg, void *workspace, size_t workspace_bytes, void *stream);
 
-/* The size class of these parameters (static storage, never NULL): "tile256x256" (SQ_DYNAMIC_TIED on shapes with at
- * least 512 tiles of 256 tokens x 256 output channels), "tile128x256" (more than 128 tiles of that size),
- * "tile128x128" (fewer), "tile64x64" (M <= 64), "tile64x128" (33 <= M <= 64 and N >= 25473), "stream32" (dynamic mode,
- * M <= 32, K % 128 == 0), or "invalid".  Informational.  The classes name the largest tile a shape of theirs is run
- * with; inside a class the kernel is chosen by how many workgroups each tile gives (up to 32 tokens, and up to 64 on
- * layers of at most 8192 channels: the few-token kernel, whose waves share K). */
+/* Which of its kernels sq_gemm / sq_linear run for these parameters (static storage, never NULL), by the workgroup's tokens x
+ * output channels: "tile256x256" (SQ_DYNAMIC_TIED only), "tile128x256", "tile128x128", "tile64x128", "tile64x64"; the tile
+ * is the one whose rounds over the chip take least; or "few_tokens" (up to 32 tokens, up to 64 on layers of at most 8192
+ * channels); or "invalid".  Informational: tests use it to state which kernel a case covers.  sq_dense_w4a8_gemm runs what
+ * SQ_DYNAMIC_TIED does at its M and N. */
 const char *sq_gemm_variant(const sq_params *p);
 
 /* sq_encode into the workspace followed by sq_gemm: Y = SQ(X) . W^T, everything on `stream`.

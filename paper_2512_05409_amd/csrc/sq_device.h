@@ -100,8 +100,8 @@ int launch_gemm(const GemmArgs& g, hipStream_t st);
 bool gemm_few_supports(int M, int N);
 int init_gemm_few_kernels();
 int launch_gemm_few(const GemmArgs& g, int mode, hipStream_t st);
-// Name of a shape's size class ("tile256x256", "tile128x256", "tile128x128", "tile64x128", "tile64x64", "stream32").
-// dynamic: two products in one loop; single: one product (tied scales, plain W4A8).
-const char* gemm_variant_name(int M, int N, int K, bool dynamic, bool single);
+// Name of the kernel launch_gemm runs for a shape ("tile256x256", "tile128x256", "tile128x128", "tile64x128", "tile64x64",
+// "few_tokens").  single: one product (tied scales, plain W4A8).
+const char* gemm_variant_name(int M, int N, bool single);
 
 }  // namespace sq

@@ -675,14 +675,16 @@ int init_gemm_kernels() {
   return e == hipSuccess ? init_gemm_few_kernels() : SQ_ERR_LAUNCH;
 }
 
-// The size class of a shape (what sq_gemm_variant reports): by the number of 128 x 256 tiles and of tokens.
-const char* gemm_variant_name(int M, int N, int K, bool dynamic, bool single) {
-  if (M <= 64) {
-    if (dynamic && M <= 32 && K % KS == 0) return "stream32";
-    return (M > 32 && (N + 127) / 128 >= 200) ? "tile64x128" : "tile64x64";
+// What sq_gemm_variant reports: the choice launch_gemm makes.
+const char* gemm_variant_name(int M, int N, bool single) {
+  switch (pick_variant(M, N, single)) {
+    case V_HUGE: return "tile256x256";
+    case V_BIG: return "tile128x256";
+    case V_MID: return "tile128x128";
+    case V_SMALL_WIDE: return "tile64x128";
+    case V_SMALL: return "tile64x64";
+    default: return "few_tokens";
   }
-  if (single && static_cast<int64_t>((M + 255) / 256) * ((N + 255) / 256) >= kHugeMinTiles) return "tile256x256";
-  return static_cast<int64_t>((M + 127) / 128) * ((N + 255) / 256) <= 128 ? "tile128x128" : "tile128x256";
 }
 
 int launch_gemm(const GemmArgs& g, hipStream_t st) {

@@ -187,16 +187,22 @@ def test_binding_refuses_host_tensors():
 
 def test_gemm_variant_names(L):
     """Which kernel a shape runs on (the GPU tests use this to state what they cover)."""
-    assert sq.sq_gemm_variant(sq.params(4096, 4096, 22016)) == "tile128x256"      # 32 x 86 tiles
-    assert sq.sq_gemm_variant(sq.params(1500, 320, 6100)) == "tile128x256"        # 12 x 24 tiles
-    assert sq.sq_gemm_variant(sq.params(200, 1024, 300)) == "tile128x128"
-    assert sq.sq_gemm_variant(sq.params(64, 8192, 28672)) == "tile64x128"
-    assert sq.sq_gemm_variant(sq.params(64, 8192, 4096)) == "tile64x64"
-    assert sq.sq_gemm_variant(sq.params(20, 8192 + 64, 28672)) == "tile64x64"
-    assert sq.sq_gemm_variant(sq.params(8, 8192, 28672)) == "stream32"
-    assert sq.sq_gemm_variant(sq.params(8, 8192 + 64, 28672)) == "tile64x64"      # K % 128 != 0
-    assert sq.sq_gemm_variant(sq.params(8, 8192, 28672, mode=sq.SQ_STATIC)) == "tile64x64"
+    def name(M, N, mode=sq.SQ_DYNAMIC, K=512):
+        return sq.sq_gemm_variant(sq.params(M, K, N, mode=mode))
+
+    assert name(4096, 22016) == "tile128x256"      # 32 x 86 tiles
+    assert name(1000, 8100) == "tile128x256"       # 8 x 32: one round
+    assert name(1500, 6100) == "tile128x128"       # 12 x 48 tiles, three rounds of 27 against two of 46
+    assert name(1300, 6100) == "tile64x128"        # 21 x 48 tiles, four rounds of 18
+    assert name(200, 300) == "tile64x64"
+    assert name(64, 28672) == "tile64x128"
+    assert name(40, 20000) == "tile64x128"
+    assert name(40, 12300) == "tile64x64"
+    assert name(64, 4096) == "few_tokens"
+    assert name(32, 28672) == name(1, 28672, K=576) == name(8, 28672, mode=sq.SQ_STATIC) == "few_tokens"
+    assert name(33, 8193) == "tile64x64" and name(33, 8192) == "few_tokens" and name(65, 64) == "tile64x64"
     assert sq.sq_gemm_variant(sq.params(8, 100, 64)) == "invalid"
-    assert sq.sq_gemm_variant(sq.params(4096, 4096, 22016, mode=sq.SQ_DYNAMIC_TIED)) == "tile256x256"   # 16 x 86 tiles
-    assert sq.sq_gemm_variant(sq.params(1500, 512, 6100, mode=sq.SQ_DYNAMIC_TIED)) == "tile128x256"
-    assert sq.sq_gemm_variant(sq.params(8, 8192, 28672, mode=sq.SQ_DYNAMIC_TIED)) == "tile64x64"
+    assert name(4096, 22016, mode=sq.SQ_DYNAMIC_TIED) == "tile256x256"   # 16 x 86 tiles
+    assert name(1000, 8100, mode=sq.SQ_DYNAMIC_TIED) == "tile128x256"
+    assert name(1500, 6100, mode=sq.SQ_DYNAMIC_TIED) == "tile128x128"
+    assert name(8, 28672, mode=sq.SQ_DYNAMIC_TIED) == "few_tokens"

@@ -1,7 +1,7 @@
-"""Full-coverage parity for the 128 x 256 workgroup tile (the kernel the benchmark configurations run).
+"""Full-coverage parity for the 128 x 256 workgroup tile (the kernel the benchmark configurations run) and the 128 x 128 one.
 
-The tile is picked only for shapes with more than 128 such tiles, so these cases have many tiles (12 x 24 and
-more: several rounds of workgroups over the chip, ragged last tile row and tile column, the XCD-aware
+A tile is picked for the shapes whose rounds over the chip it makes shortest, so these cases have many tiles (one and two
+rounds of the 128 x 256 tile, three of the 128 x 128 one; ragged last tile row and tile column, the XCD-aware
 workgroup-to-tile mapping on a large grid) and a short K, which lets the oracle compute EVERY row and column.
 Both accumulators, the fp32 and the bf16 output are compared element by element, in all three modes of the
 kernel: dynamic (low + zero-padded high in one loop), static (low loop, then the compact high loop) and the
@@ -36,25 +36,30 @@ def check_all(p, enc, wq, sw, prepacked=None, static_mask=None):
     assert np.array_equal(y16, prod.ybf16), "bf16 output"
 
 
-@pytest.mark.parametrize("M,K,N,bank,topk", [(1500, 320, 6100, 64, 8),    # 3 K steps, the last one partial
-                                             (1409, 256, 5900, 32, 4),    # 2 K steps: no steady-state iteration
-                                             (1300, 640, 6200, 64, 8),    # 5 K steps: steady state + every peeled tail
-                                             (1537, 1024, 8200, 128, 16)])  # 8 K steps, M one row past a tile edge
-def test_big_tile_dynamic_every_element(M, K, N, bank, topk):
-    _say(f"big tile dynamic M={M} K={K} N={N} bank={bank} topk={topk}")
+BIG, MID = "tile128x256", "tile128x128"
+
+
+@pytest.mark.parametrize("M,K,N,bank,topk,variant", [
+    (1000, 320, 8100, 64, 8, BIG), (1500, 320, 6100, 64, 8, MID),    # 3 K steps, the last one partial
+    (1009, 256, 8100, 32, 4, BIG), (1409, 256, 5900, 32, 4, MID),    # 2 K steps: no steady-state iteration
+    (1000, 640, 8180, 64, 8, BIG), (1300, 640, 6200, 64, 8, MID),    # 5 K steps: steady state + every peeled tail
+    (1537, 1024, 8200, 128, 16, BIG)])                               # 8 K steps, M one row past a tile edge, two rounds
+def test_big_tile_dynamic_every_element(M, K, N, bank, topk, variant):
+    _say(f"big tile dynamic M={M} K={K} N={N} bank={bank} topk={topk} ({variant})")
     p = sq.params(M, K, N, bank, topk, out_dtype=sq.SQ_OUT_F32)
-    assert sq.sq_gemm_variant(p) == "tile128x256"
+    assert sq.sq_gemm_variant(p) == variant
     bits, wq, sw = random_case(5000 + M + K + N, M, K, N, outliers=4)
     check_all(p, oracle.encode(bits, bank, topk), wq, sw)
 
 
-@pytest.mark.parametrize("M,K,N,bank,topk", [(1500, 256, 6100, 64, 8),    # K_hi = 32: one partial high step
-                                             (1409, 512, 5900, 32, 4),    # K_hi = 64
-                                             (1300, 1024, 6200, 64, 16)])  # K_hi = 256: two high steps
-def test_big_tile_static_every_element(M, K, N, bank, topk):
-    _say(f"big tile static M={M} K={K} N={N} bank={bank} topk={topk}")
+@pytest.mark.parametrize("M,K,N,bank,topk,variant", [
+    (1000, 256, 8100, 64, 8, BIG), (1500, 256, 6100, 64, 8, MID),     # K_hi = 32: one partial high step
+    (1009, 512, 8100, 32, 4, BIG), (1409, 512, 5900, 32, 4, MID),     # K_hi = 64
+    (1537, 1024, 8200, 64, 16, BIG), (1300, 1024, 6200, 64, 16, MID)])  # K_hi = 256: two high steps
+def test_big_tile_static_every_element(M, K, N, bank, topk, variant):
+    _say(f"big tile static M={M} K={K} N={N} bank={bank} topk={topk} ({variant})")
     p = sq.params(M, K, N, bank, topk, mode=sq.SQ_STATIC, out_dtype=sq.SQ_OUT_F32)
-    assert sq.sq_gemm_variant(p) == "tile128x256"
+    assert sq.sq_gemm_variant(p) == variant
     bits, wq, sw = random_case(6000 + M + K + N, M, K, N, outliers=4)
     mask = make_static_mask(K, bank, topk, seed=K + N)
     enc = oracle.encode(bits, bank, topk, static_mask=mask)
@@ -63,14 +68,15 @@ def test_big_tile_static_every_element(M, K, N, bank, topk):
     check_all(p, enc, wq, sw, prepacked=pre, static_mask=mask)
 
 
-@pytest.mark.parametrize("M,K,N", [(1500, 320, 6100), (1300, 640, 6200)])
+@pytest.mark.parametrize("M,K,N,variant", [(1000, 320, 8100, BIG), (1537, 640, 8200, BIG), (1000, 1152, 8100, BIG),
+                                           (1500, 320, 6100, MID), (1300, 640, 6200, MID)])
 @pytest.mark.parametrize("out_dtype", [sq.SQ_OUT_F32, sq.SQ_OUT_BF16])
-def test_big_tile_dense_w4a8_every_element(M, K, N, out_dtype):
+def test_big_tile_dense_w4a8_every_element(M, K, N, variant, out_dtype):
     """The plain W4A8 reference of the benchmark on the same tile, against an exact integer matmul (float64 BLAS
     on integers below 2^53 is exact) and the two-multiplication epilogue written out in numpy."""
-    _say(f"big tile dense w4a8 M={M} K={K} N={N} out={out_dtype}")
+    _say(f"big tile dense w4a8 M={M} K={K} N={N} out={out_dtype} ({variant})")
     p = sq.params(M, K, N, out_dtype=out_dtype)
-    assert sq.sq_gemm_variant(p) == "tile128x256"
+    assert sq.sq_gemm_variant(sq.params(M, 512, N, mode=sq.SQ_DYNAMIC_TIED)) == variant  # the single-product modes' choice
     rng = np.random.default_rng(M + K + N)
     a = rng.integers(-127, 128, size=(M, K)).astype(np.int8)
     sa = rng.uniform(0.01, 0.1, M).astype(np.float32)
@@ -95,8 +101,9 @@ def test_big_tile_dense_w4a8_every_element(M, K, N, out_dtype):
 
 # ---- leading dimension of Y: padded rows (vector stores when the rows stay 16-byte aligned, element stores
 # otherwise), on every kernel variant; the padding columns must keep their canary ----
-@pytest.mark.parametrize("M,K,N,variant", [(1300, 256, 6100, "tile128x256"), (200, 512, 300, "tile128x128"),
-                                           (50, 512, 200, "tile64x64"), (8, 512, 200, "stream32")])
+@pytest.mark.parametrize("M,K,N,variant", [(1000, 256, 8100, BIG), (1500, 256, 6100, MID), (1300, 256, 6100, "tile64x128"),
+                                           (200, 512, 300, "tile64x64"), (50, 512, 200, "few_tokens"),
+                                           (8, 512, 200, "few_tokens")])
 @pytest.mark.parametrize("pad", [8, 3])
 @pytest.mark.parametrize("out_dtype", [sq.SQ_OUT_F32, sq.SQ_OUT_BF16])
 def test_output_leading_dimension(M, K, N, variant, pad, out_dtype):
@@ -130,8 +137,8 @@ def test_output_leading_dimension(M, K, N, variant, pad, out_dtype):
         assert (got[:, N:] == 0xA5A5).all(), "padding columns were written"
 
 
-@pytest.mark.parametrize("M,N,variant", [(1300, 6100, "tile128x256"), (200, 300, "tile128x128"), (50, 200, "tile64x64"),
-                                         (8, 200, "stream32")])
+@pytest.mark.parametrize("M,N,variant", [(1000, 8100, BIG), (1500, 6100, MID), (1300, 6100, "tile64x128"),
+                                         (200, 300, "tile64x64"), (50, 200, "few_tokens"), (8, 200, "few_tokens")])
 def test_tiny_magnitude_rows(M, N, variant):
     """Rows whose values are around 1e-30 (per-token scales near 2^-103 and 2^-107): the epilogue must still
     give the oracle's bits, i.e. no intermediate of the dequantisation may leave the normal fp32 range."""

@@ -147,10 +147,8 @@ def run_gemm(p, enc_host, wq, sw, out_dtype, prepacked=None, static_mask=None):
     return yh, alo.host(np.int32).reshape(M, N), ahi.host(np.int32).reshape(M, N)
 
 
-# shapes chosen to reach the small kernel variants: the 128x128 tile (M > 64 with few tiles), the 64x64 tile
-# (32 < M <= 64, or M <= 32 with K % 128 != 0), the weight-streaming kernel (M <= 32, K % 128 == 0) with
-# 1 ... 26 K steps (fewer than its rings hold, exactly as many, the first trip of the steady state, several
-# tail lengths), ragged M / N / K edges.  The 128x256 tile needs more than 128 tiles: test_gpu_big_tile.py.
+# small shapes: the 64x64 tile (M > 64) and the few-token kernel with 1 ... 26 K steps shared among its waves, ragged
+# M / N / K edges.  The larger tiles need larger shapes: test_gpu_split_k.py, test_gpu_big_tile.py.
 @pytest.mark.parametrize("M,K,N,bank,topk", [(16, 512, 512, 64, 8), (200, 1024, 300, 64, 8), (129, 320, 130, 32, 4),
                                              (64, 2048, 256, 128, 16), (1, 512, 128, 64, 8), (257, 64, 5, 64, 16),
                                              (5, 384, 130, 64, 8), (32, 2048, 70, 64, 16), (8, 320, 96, 32, 8),
@@ -434,10 +432,10 @@ def test_static_long_rows(K, bank, topk):
 
 
 @pytest.mark.parametrize("M,K,N", [(1, 1024, 200), (8, 2048, 130), (32, 1280, 96)])
-def test_static_decode_shapes_take_the_streaming_kernel(M, K, N):
-    """Static mode with at most 32 tokens: given a workspace, sq_gemm builds the image of the high part from
-    hi_val and the channel mask and runs the weight-streaming kernel on the dense low part: same accumulators,
-    same outputs as the oracle; without a workspace the generic tile gives the same bytes."""
+def test_static_decode_shapes(M, K, N):
+    """Static mode with at most 32 tokens from the dense low part (the few-token kernel: the low product over K, then the
+    compact high one): accumulators and outputs are the oracle's, with the workspace that sq_gemm_workspace_bytes asks for
+    and without one (it is not used).  The compact low part is test_static_reordered_operands' and sq_linear's."""
     _say(f"static decode M={M} K={K} N={N}")
     bank, topk = 64, 8
     bits, wq, sw = random_case(2700 + M + K + N, M, K, N, outliers=4)
@@ -445,7 +443,7 @@ def test_static_decode_shapes_take_the_streaming_kernel(M, K, N):
     enc = oracle.encode(bits, bank, topk, static_mask=mask)
     prod = oracle.gemm(enc, wq, sw)
     p = sq.params(M, K, N, bank, topk, mode=sq.SQ_STATIC, out_dtype=sq.SQ_OUT_F32)
-    assert sq.sq_gemm_workspace_bytes(p) >= M * K
+    assert sq.sq_gemm_variant(p) == "few_tokens" and sq.sq_gemm_workspace_bytes(p) >= M * K
     wqd, md = dev(wq), dev(mask)
     pre = torch.empty(sq.sq_weight_prepack_bytes(p), dtype=torch.uint8, device="cuda")
     sq.sq_weight_prepack(p, wqd, None, md, pre)

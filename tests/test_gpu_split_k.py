@@ -68,16 +68,18 @@ def test_few_tokens_channel_tails(M, K, bank, topk, mode):
 
 
 TILE_SHAPES = [(65, 64, 70), (130, 128, 515), (100, 192, 260), (333, 1152, 300), (300, 320, 4095), (64, 1024, 8200),
-               (40, 384, 12300), (200, 2048, 12300)]
+               (40, 384, 12300), (200, 2048, 8000)]
 
 
 @pytest.mark.parametrize("M,K,N,mode", [s + (m,) for s in TILE_SHAPES for m in (sq.SQ_DYNAMIC, sq.SQ_STATIC)]
                          + [s + (sq.SQ_DYNAMIC_TIED,) for s in TILE_SHAPES if s[1] & (s[1] - 1) == 0])
 def test_tiles_with_two_k_groups(M, K, N, mode):
+    assert sq.sq_gemm_variant(sq.params(M, K, N, 64, 32, mode=mode)) in ("tile64x64", "tile64x128")
     check(M, K, N, 64, 32, mode)
 
 
 # the 128 x 256 tile with padded and unaligned rows of Y (8 x 32 of its tiles: one round over the chip)
 @pytest.mark.parametrize("mode", [sq.SQ_DYNAMIC, sq.SQ_STATIC])
 def test_large_tile_rows_of_y(mode):
+    assert sq.sq_gemm_variant(sq.params(1000, 256, 8100, 64, 8, mode=mode)) == "tile128x256"
     check(1000, 256, 8100, 64, 8, mode)

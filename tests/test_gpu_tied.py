@@ -71,7 +71,8 @@ def run_gemm_tied(p, enc, wq, sw, out_dtype, with_image):
 
 @pytest.mark.parametrize("M,K,N,bank,topk", [(16, 512, 512, 64, 8), (200, 1024, 300, 64, 8), (129, 256, 130, 32, 4),
                                              (64, 2048, 256, 128, 16), (1, 512, 128, 64, 8), (33, 2048, 70, 64, 16),
-                                             (1500, 512, 6100, 64, 8), (1300, 1024, 6200, 32, 8)])
+                                             (1500, 512, 6100, 64, 8), (1300, 1024, 6200, 32, 8),
+                                             (1000, 64, 8100, 64, 16), (1537, 1024, 8200, 32, 8)])  # the 128 x 256 tile
 @pytest.mark.parametrize("with_image", [True, False])
 def test_gemm_tied_every_element(M, K, N, bank, topk, with_image):
     """with_image: the combined operand comes from the caller; otherwise sq_gemm builds it from the format."""
