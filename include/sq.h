@@ -214,6 +214,11 @@ int sq_gemm(const sq_params *p, const sq_act *a, const sq_weight *w, void *y, in
  * SQ_DYNAMIC_TIED does at its M and N. */
 const char *sq_gemm_variant(const sq_params *p);
 
+/* Which of its kernels sq_encode / sq_linear run for these parameters (static storage, never NULL): dynamic modes
+ * "few_banks", "streaming" or "general" (sq_encode_few.hip, sq_encode_dyn.hip, sq_encode.hip), static mode "static_rows" or,
+ * for rows that do not fit in LDS, "static_general"; or "invalid".  Informational, as sq_gemm_variant. */
+const char *sq_encode_variant(const sq_params *p);
+
 /* sq_encode into the workspace followed by sq_gemm: Y = SQ(X) . W^T, everything on `stream`.
  * workspace: device, 256-byte aligned, sq_linear_workspace_bytes(p) bytes, contents destroyed. */
 int sq_linear(const sq_params *p, const uint16_t *x_bf16, int64_t ldx, const uint32_t *static_mask,

@@ -22,7 +22,7 @@ EXPORTS = (
     "sq_act_bytes", "sq_gemm_workspace_bytes", "sq_linear_workspace_bytes", "sq_weight_prepack_bytes",
     "sq_weight_prepack", "sq_encode", "sq_gemm", "sq_linear", "sq_dense_w4a8_prepack", "sq_dense_w4a8_gemm",
     "sq_calibrate_workspace_bytes", "sq_calibrate_static", "sq_probe_mfma_i8", "sq_probe_stream", "sq_status_string", "sq_version",
-    "sq_init", "sq_gemm_variant", "sq_linear_noalloc", "sq_lo_compact_bytes",
+    "sq_init", "sq_gemm_variant", "sq_encode_variant", "sq_linear_noalloc", "sq_lo_compact_bytes",
     "sq_storage_row_bytes", "sq_pack_storage", "sq_unpack_storage", "sq_probe_mfma_alt", "sq_probe_fp6_tile",
     "sq_storage_row_bytes_sentinel", "sq_pack_storage_sentinel", "sq_unpack_storage_sentinel",
     "sq_wsq_bytes", "sq_wsq_encode", "sq_wsq_prepack_bytes", "sq_wsq_prepack", "sq_quantize_act", "sq_wsq_gemm",
@@ -127,6 +127,8 @@ def lib() -> ctypes.CDLL:
         L.sq_init.restype = ctypes.c_int
         L.sq_gemm_variant.argtypes = [P(sq_params)]
         L.sq_gemm_variant.restype = ctypes.c_char_p
+        L.sq_encode_variant.argtypes = [P(sq_params)]
+        L.sq_encode_variant.restype = ctypes.c_char_p
         _lib = L
     return _lib
 
@@ -145,6 +147,10 @@ def sq_init() -> None:
 
 def sq_gemm_variant(p: "sq_params") -> str:
     return lib().sq_gemm_variant(ctypes.byref(p)).decode()
+
+
+def sq_encode_variant(p: "sq_params") -> str:
+    return lib().sq_encode_variant(ctypes.byref(p)).decode()
 
 
 def params(M: int, K: int, N: int, bank: int = 64, topk: int = 8, mode: int = SQ_DYNAMIC,

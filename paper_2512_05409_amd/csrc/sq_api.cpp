@@ -121,6 +121,13 @@ const char* sq_gemm_variant(const sq_params* p) {
   return sq::gemm_variant_name(p->M, p->N, p->mode == SQ_DYNAMIC_TIED);
 }
 
+const char* sq_encode_variant(const sq_params* p) {
+  if (check_params(p) != SQ_OK) return "invalid";
+  if (p->mode == SQ_STATIC) return sq::encode_static_gather_supports(*p) ? "static_rows" : "static_general";
+  if (sq::encode_few_supports(*p)) return "few_banks";
+  return sq::encode_stream_supports(*p) ? "streaming" : "general";
+}
+
 size_t sq_act_bytes(const sq_params* p, size_t* d_lo, size_t* hi_val, size_t* mask, size_t* scale) {
   if (check_params(p) != SQ_OK) return 0;
   const ActLayout l = act_layout(p);

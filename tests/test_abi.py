@@ -206,3 +206,15 @@ def test_gemm_variant_names(L):
     assert name(1000, 8100, mode=sq.SQ_DYNAMIC_TIED) == "tile128x256"
     assert name(1500, 6100, mode=sq.SQ_DYNAMIC_TIED) == "tile128x128"
     assert name(8, 28672, mode=sq.SQ_DYNAMIC_TIED) == "few_tokens"
+
+
+def test_encode_variant_names(L):
+    """Which encoder a call runs (the GPU tests use this to state what they cover)."""
+    def name(M, K, bank=64, topk=8, mode=sq.SQ_DYNAMIC):
+        return sq.sq_encode_variant(sq.params(M, K, 64, bank, topk, mode=mode))
+
+    assert name(1, 8192) == name(128, 4096) == name(8, 11008, 128, 16) == name(64, 4096, mode=sq.SQ_DYNAMIC_TIED) == "few_banks"
+    assert name(4096, 4096) == name(4096, 4096, mode=sq.SQ_DYNAMIC_TIED) == name(3, 16384) == "streaming"
+    assert name(4096, 11008) == name(3, 16448) == "general"
+    assert name(4096, 11008, mode=sq.SQ_STATIC) == "static_rows" and name(9, 49152, 128, 16, mode=sq.SQ_STATIC) == "static_general"
+    assert name(8, 100) == "invalid"

@@ -379,8 +379,11 @@ def test_encode_padded_rows_of_x_on_the_streaming_kernels(mode):
     """ldx > K on the kernels that copy rows into LDS (K = 4096: a unit of the streaming kernel lies inside one
     row; the static kernel stages whole rows): the padding holds +inf and must never be read as data."""
     _say(f"encode ldx {mode}")
-    M, K, bank, topk, ldx = 70, 4096, 64, 8, 4096 + 24
+    M, K, bank, topk, ldx = 70 if mode == "static" else 2100, 4096, 64, 8, 4096 + 24
     bits, _, _ = random_case(77, M=M, K=K, N=8)
+    lib_mode = {"dynamic": sq.SQ_DYNAMIC, "tied": sq.SQ_DYNAMIC_TIED, "static": sq.SQ_STATIC}[mode]
+    p = sq.params(M, K, 64, bank, topk, mode=lib_mode)
+    assert sq.sq_encode_variant(p) == ("static_rows" if mode == "static" else "streaming")
     if mode == "static":
         mask = make_static_mask(K, bank, topk, seed=3)
         p, act = run_encode(bits, bank, topk, static_mask=mask, ldx=ldx)
@@ -388,8 +391,6 @@ def test_encode_padded_rows_of_x_on_the_streaming_kernels(mode):
         return
     padded = np.full((M, ldx), 0x7F80, np.uint16)
     padded[:, :K] = bits
-    lib_mode = sq.SQ_DYNAMIC if mode == "dynamic" else sq.SQ_DYNAMIC_TIED
-    p = sq.params(M, K, 64, bank, topk, mode=lib_mode)
     act = GuardedAct(p)
     sq.sq_encode(p, dev(padded), act, ldx=ldx)
     torch.cuda.synchronize()
