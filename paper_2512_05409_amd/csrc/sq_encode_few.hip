@@ -4,7 +4,9 @@
 // vector instructions, about 2 ns each, while most of the chip idles.  Here LPB neighbouring lanes share a bank: each
 // selects the k largest of its own channels (the same comparator networks), the sorted lists are merged across the lanes
 // (quad permutations; max(a_i, b_{k-1-i}) keeps the k largest of two descending lists, so that all lanes of the bank end
-// up with the same set), and each lane quantises and stores its own channels.  A workgroup is one token row.
+// up with the same set), and each lane quantises and stores its own channels.  A workgroup is one token row, or, where a
+// row has at most 32 lanes, one wave of several rows (with a wave per row most lanes idled and the wave took as long:
+// [1905,192] b = 64, k = 32 20.1 -> 6.2 us; with a lane per bank 7.7 us).
 // Bounded by that chain (about 650 instructions at bank 64, k = 8) and by launch and memory latency:
 // [1,8192] 5.7 -> 3.9 us, [64,8192] 6.3 -> 4.3 us, [128,8192] bank 128, k = 32 14.4 -> 7.5 us.
 #include "sq_encode_common.h"
@@ -21,7 +23,8 @@ constexpr int kThreads = 512;
 struct FewEncArgs {
   const uint16_t* x;
   int64_t ldx;
-  int K, G;
+  int M, K, G;
+  int lg_span;        // SHARED: lanes of a row, a power of two up to 32
   uint8_t* d_lo;
   int8_t* hi_val;
   uint32_t* mask;
@@ -39,14 +42,15 @@ __device__ __forceinline__ uint32_t quad_xor(uint32_t v) {
 __device__ __forceinline__ uint32_t pk_max_u16(uint32_t a, uint32_t b) {
   return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b)));
 }
-// maximum over the wave, both halves of the word for themselves
-__device__ __forceinline__ uint32_t wave_pk_max(uint32_t v) {
+// maximum over every 2^lg lanes (lg = 1 ... 6), both halves of the word for themselves
+__device__ __forceinline__ uint32_t span_pk_max(uint32_t v, int lg) {
   v = pk_max_u16(v, quad_xor<1>(v));
-  v = pk_max_u16(v, quad_xor<2>(v));
-  v = pk_max_u16(v, static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(static_cast<int>(v), 0x141, 0xF, 0xF, true)));  // row_half_mirror
-  v = pk_max_u16(v, static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(static_cast<int>(v), 0x140, 0xF, 0xF, true)));  // row_mirror
-  v = pk_max_u16(v, static_cast<uint32_t>(__shfl_xor(static_cast<int>(v), 16, 64)));
-  return pk_max_u16(v, static_cast<uint32_t>(__shfl_xor(static_cast<int>(v), 32, 64)));
+  if (lg > 1) v = pk_max_u16(v, quad_xor<2>(v));
+  if (lg > 2) v = pk_max_u16(v, static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(static_cast<int>(v), 0x141, 0xF, 0xF, true)));  // row_half_mirror
+  if (lg > 3) v = pk_max_u16(v, static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(static_cast<int>(v), 0x140, 0xF, 0xF, true)));  // row_mirror
+  if (lg > 4) v = pk_max_u16(v, static_cast<uint32_t>(__shfl_xor(static_cast<int>(v), 16, 64)));
+  if (lg > 5) v = pk_max_u16(v, static_cast<uint32_t>(__shfl_xor(static_cast<int>(v), 32, 64)));
+  return v;
 }
 
 // One round of the merge across lanes: `a` (descending) against the list of lane ^ X.
@@ -71,20 +75,22 @@ __device__ __forceinline__ uint32_t spread_even_bits_to_bytes(uint32_t b) {
 template <int B, int KT>
 constexpr int lanes_per_bank() { return B / KT >= 4 ? 4 : 2; }
 
-template <int B, int KT, bool TIED>
-__global__ __launch_bounds__(kThreads) void encode_few_kernel(FewEncArgs a) {
+// SHARED: a workgroup is one wave of 64 >> lg_span rows; otherwise it is one row.
+template <int B, int KT, bool TIED, bool SHARED>
+__global__ __launch_bounds__(SHARED ? 64 : kThreads) void encode_few_kernel(FewEncArgs a) {
   constexpr int LPB = lanes_per_bank<B, KT>(), N = B / LPB;  // channels per lane
   static_assert(N >= KT && N % 8 == 0, "a lane's channels hold the k largest, and whole groups of eight");
-  __shared__ uint32_t part[kThreads / 64];
   const int tid = threadIdx.x, lane = tid & 63;
-  const int g = tid / LPB, q = tid % LPB;
-  const bool active = g < a.G;
-  const int64_t row = blockIdx.x;
+  const int at = SHARED ? tid & ((1 << a.lg_span) - 1) : tid;  // lane inside the row
+  const int g = at / LPB, q = at % LPB;
+  const int64_t row = SHARED ? (static_cast<int64_t>(blockIdx.x) << (6 - a.lg_span)) + (tid >> a.lg_span) : blockIdx.x;
+  const bool active = g < a.G && (!SHARED || row < a.M);
   const int c0 = q * N;  // first channel of this lane inside the bank
 
   uint32_t xr[N / 2];  // bf16 pairs
   {
-    const uint4* src = reinterpret_cast<const uint4*>(a.x + row * a.ldx + static_cast<int64_t>(active ? g : a.G - 1) * B + c0);
+    const uint4* src = reinterpret_cast<const uint4*>(a.x + (SHARED ? min(row, static_cast<int64_t>(a.M - 1)) : row) * a.ldx +
+                                                      static_cast<int64_t>(g < a.G ? g : a.G - 1) * B + c0);
 #pragma unroll
     for (int i = 0; i < N / 8; ++i) {
       const uint4 v = src[i];
@@ -131,10 +137,13 @@ __global__ __launch_bounds__(kThreads) void encode_few_kernel(FewEncArgs a) {
   for (int i = 1; i < KT; ++i) tmax = umax(tmax, top[i]);
 
   // ---- the row's maxima, per-token scales ----
-  uint32_t mx = wave_pk_max(active ? (key_magnitude(tmax) << 16) | key_magnitude(dropped) : 0u);
-  if (lane == 0) part[tid >> 6] = mx;
-  __syncthreads();
-  for (int w = 0; w < static_cast<int>(blockDim.x) / 64; ++w) mx = pk_max_u16(mx, part[w]);
+  uint32_t mx = span_pk_max(active ? (key_magnitude(tmax) << 16) | key_magnitude(dropped) : 0u, SHARED ? a.lg_span : 6);
+  if constexpr (!SHARED) {
+    __shared__ uint32_t part[kThreads / 64];
+    if (lane == 0) part[tid >> 6] = mx;
+    __syncthreads();
+    for (int w = 0; w < static_cast<int>(blockDim.x) / 64; ++w) mx = pk_max_u16(mx, part[w]);
+  }
   if (!active) return;
   const uint32_t mag_hi = mx >> 16, mag_lo = mx & 0xFFFFu;
   const float amax_hi = __uint_as_float(mag_hi << 16), amax_lo = __uint_as_float(mag_lo << 16);
@@ -152,7 +161,7 @@ __global__ __launch_bounds__(kThreads) void encode_few_kernel(FewEncArgs a) {
     sc_hi = mag_hi ? amax_hi / a.q_hi : 1.0f;
     sc_lo = mag_lo ? amax_lo / a.q_lo : 1.0f;
   }
-  if (tid == 0) {
+  if (at == 0) {
     a.s_hi[row] = sc_hi;
     a.s_lo[row] = sc_lo;
   }
@@ -215,28 +224,53 @@ __global__ __launch_bounds__(kThreads) void encode_few_kernel(FewEncArgs a) {
   if (a.image) store_bytes<N>(a.image + row * a.K + static_cast<int64_t>(g) * B + c0, im);
 }
 
+// Threads of a row of `lanes` lanes.
+int span_of(int lanes) {
+  if (lanes > 32) return (lanes + 63) / 64 * 64;
+  int span = 2;
+  while (span < lanes) span *= 2;
+  return span;
+}
+
 template <int B, int KT>
-int launch_few_enc(const sq_params& p, const FewEncArgs& a, bool tied, hipStream_t st) {
-  const int threads = (a.G * lanes_per_bank<B, KT>() + 63) / 64 * 64;
-  if (tied) hipLaunchKernelGGL((encode_few_kernel<B, KT, true>), dim3(p.M), dim3(threads), 0, st, a);
-  else hipLaunchKernelGGL((encode_few_kernel<B, KT, false>), dim3(p.M), dim3(threads), 0, st, a);
+int launch_few_enc(const sq_params& p, FewEncArgs a, bool tied, hipStream_t st) {
+  const int span = span_of(a.G * lanes_per_bank<B, KT>());
+  if (span < 64) {
+    const int rows = 64 / span;
+    const dim3 grid((p.M + rows - 1) / rows);
+    a.lg_span = __builtin_ctz(span);
+    if (tied) hipLaunchKernelGGL((encode_few_kernel<B, KT, true, true>), grid, dim3(64), 0, st, a);
+    else hipLaunchKernelGGL((encode_few_kernel<B, KT, false, true>), grid, dim3(64), 0, st, a);
+  } else {
+    a.lg_span = 6;
+    if (tied) hipLaunchKernelGGL((encode_few_kernel<B, KT, true, false>), dim3(p.M), dim3(span), 0, st, a);
+    else hipLaunchKernelGGL((encode_few_kernel<B, KT, false, false>), dim3(p.M), dim3(span), 0, st, a);
+  }
   return hipGetLastError() == hipSuccess ? SQ_OK : SQ_ERR_LAUNCH;
 }
 
 }  // namespace
 
-// Up to eight waves per compute unit (rows per unit times waves per row).  Splitting a bank costs about 1.7 times its
-// instructions in all, so beyond that the other encoders are ahead: 8 waves [256,8192] 4.7 against 6.5 us, 10 waves
-// [300,5120] 6.0 against 5.7 us, 22 waves [333,11008] 9.3 against 8.3 us.
+// Which calls.  Splitting a bank in four costs about 1.7 times its instructions in all, so up to eight waves per compute unit
+// (workgroups per unit times waves each): 8 waves [256,8192] 4.7 against 6.5 us, 10 waves [300,5120] 6.0 against 5.7 us,
+// 22 waves [333,11008] 9.3 against 8.3 us.  Split in two the chain is hardly shorter, so only while no SIMD has two waves:
+// k = 32 of b = 64 [1024,2048] 6.8 against 9.2 us, but [2048,2048] 10.3 against 9.3 us; and several workgroups of more than
+// one wave do not spread evenly over the SIMDs ([512,4096] 9.6 against 8.7 us).  Rows of b = 32 that leave lanes of a shared
+// wave idle lose from the fifth wave on ([2202,192] 3.8 against 3.7 us).
 bool encode_few_supports(const sq_params& p) {
-  const int lanes = p.K / p.bank * (p.bank / p.topk >= 4 ? 4 : 2), cus = device_compute_units();
-  return lanes <= kThreads && static_cast<int64_t>((p.M + cus - 1) / cus) * ((lanes + 63) / 64) <= 8;
+  const int lpb = p.bank / p.topk >= 4 ? 4 : 2, lanes = p.K / p.bank * lpb, cus = device_compute_units();
+  if (lanes > kThreads) return false;
+  const int span = span_of(lanes), waves = (span + 63) / 64, rows = span < 64 ? 64 / span : 1;
+  const int64_t groups = (p.M + rows - 1) / rows, per_cu = (groups + cus - 1) / cus;  // workgroups in all, and per compute unit
+  if (lpb == 2) return per_cu * waves <= 4 && (per_cu == 1 || waves == 1);
+  return per_cu * waves <= (p.bank == 32 && span < 64 && lanes < span ? 4 : 8);
 }
 
 int launch_encode_few(const sq_params& p, const uint16_t* x, int64_t ldx, const sq_act& out, bool tied, hipStream_t st) {
   FewEncArgs a;
   a.x = x;
   a.ldx = ldx;
+  a.M = p.M;
   a.K = p.K;
   a.G = p.K / p.bank;
   a.d_lo = out.d_lo;

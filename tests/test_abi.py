@@ -218,3 +218,16 @@ def test_encode_variant_names(L):
     assert name(4096, 11008) == name(3, 16448) == "general"
     assert name(4096, 11008, mode=sq.SQ_STATIC) == "static_rows" and name(9, 49152, 128, 16, mode=sq.SQ_STATIC) == "static_general"
     assert name(8, 100) == "invalid"
+
+
+def test_short_rows_share_waves_in_the_few_bank_encoder(L):
+    """The few-bank encoder is ahead of the others while no more than eight waves of useful lanes (four where only two lanes
+    share a bank) fall to a compute unit: shapes on either side, which the others encode faster when it takes them and
+    wastes lanes, or takes them at eight waves of two lanes per bank."""
+    def few(M, K, bank, topk):
+        return sq.sq_encode_variant(sq.params(M, K, 64, bank, topk)) == "few_banks"
+
+    assert few(2048, 1024, 64, 8) and not few(2049, 1024, 64, 8)
+    assert few(4096, 512, 64, 8) and not few(4112, 512, 64, 8)      # 32 lanes a row: two rows a wave
+    assert few(1024, 2048, 64, 32) and not few(1025, 2048, 64, 32)  # two lanes a bank: four waves
+    assert not few(512, 4096, 64, 32) and not few(267, 4096, 64, 32) and not few(331, 8192, 64, 32) and not few(72, 11008, 64, 32)

@@ -1,5 +1,6 @@
 """The encoder for few banks (several lanes per bank): every format, with the matrix-core image, two scales and tied, odd
-bank counts, rows that fill its eight waves and the first shapes past its rule -- against the oracle, bit for bit."""
+bank counts, several rows per wave (with lanes to spare and without, the last wave not full), rows that fill its eight
+waves, the last calls of its rule and the first past it -- against the oracle, bit for bit."""
 import numpy as np
 import pytest
 import torch
@@ -50,4 +51,24 @@ def test_formats(bank, topk, tied):
                                            (256, 8192, 64, 8), (257, 8192, 64, 8), (2, 8256, 64, 8), (520, 4096, 128, 8),
                                            (2048, 512, 64, 8), (2049, 512, 64, 16)])
 def test_shapes(M, K, bank, topk):
+    check(M, K, bank, topk)
+
+
+@pytest.mark.parametrize("K,bank,topk", [(64, 64, 32), (64, 32, 16), (128, 128, 8), (192, 64, 8), (192, 64, 32), (256, 128, 32),
+                                         (320, 32, 16), (512, 32, 16), (576, 64, 8), (640, 128, 16), (1024, 128, 32),
+                                         (1152, 64, 32), (2048, 64, 32)])
+@pytest.mark.parametrize("M", [1, 3, 67, 301])
+def test_rows_that_share_a_wave(M, K, bank, topk):
+    assert sq.sq_encode_variant(sq.params(M, K, 64, bank, topk)) == "few_banks"
+    check(M, K, bank, topk)
+    if K // bank & (K // bank - 1) == 0:
+        check(M, K, bank, topk, tied=True)
+
+
+# the rule: eight waves per compute unit (256 of them), four where two lanes share a bank; short rows share waves
+@pytest.mark.parametrize("M,K,bank,topk", [(2048, 1024, 64, 8), (4096, 512, 64, 8), (1024, 2048, 64, 32), (2048, 1024, 64, 32),
+                                           (256, 4096, 64, 32), (256, 8192, 64, 32)])
+def test_ends_of_the_rule(M, K, bank, topk):
+    for m, kernel in ((M, "few_banks"), (M + 16, "streaming")):
+        assert sq.sq_encode_variant(sq.params(m, K, 64, bank, topk)) == kernel
     check(M, K, bank, topk)

@@ -44,21 +44,21 @@ def check(kernel, M, K, bank, topk, tied=False, pair=(8, 4), pad=0, rows=None):
 
 @pytest.mark.parametrize("bank,topk", FORMATS)
 @pytest.mark.parametrize("tied", [False, True])
-@pytest.mark.parametrize("M,K,pad", [(2311, 512, 0), (2100, 1024, 24)])
+@pytest.mark.parametrize("M,K,pad", [(8311, 512, 0), (4200, 1024, 24)])
 def test_streaming_formats(M, K, pad, bank, topk, tied):
     check("streaming", M, K, bank, topk, tied, pad=pad, rows=sample(M, 150) if tied else None)
 
 
 @pytest.mark.parametrize("bank,topk", FORMATS)
-@pytest.mark.parametrize("M,K,pad", [(2100, 1152, 0), (2311, 384, 8)])
+@pytest.mark.parametrize("M,K,pad", [(2100, 1152, 0), (8311, 384, 8)])
 def test_general_formats(M, K, pad, bank, topk):
     check("general", M, K, bank, topk, pad=pad)
 
 
 @pytest.mark.parametrize("pair", [(8, 3), (8, 2), (4, 2)])
 @pytest.mark.parametrize("kernel,M,K,bank,topk", [
-    ("streaming", 3, 16384, 64, 8), ("streaming", 3, 8192, 32, 4), ("streaming", 2100, 512, 64, 32), ("streaming", 2100, 512, 32, 16),
-    ("streaming", 2100, 1024, 128, 16), ("general", 3, 16448, 64, 8), ("general", 5, 11008, 32, 2), ("general", 2100, 1152, 128, 32),
-    ("general", 2100, 320, 64, 16)])
+    ("streaming", 3, 16384, 64, 8), ("streaming", 3, 8192, 32, 4), ("streaming", 4200, 512, 64, 32), ("streaming", 4200, 512, 32, 16),
+    ("streaming", 4200, 1024, 128, 16), ("general", 3, 16448, 64, 8), ("general", 5, 11008, 32, 2), ("general", 2100, 1152, 128, 32),
+    ("general", 4200, 320, 64, 16)])
 def test_precision_pairs(kernel, M, K, bank, topk, pair):
     check(kernel, M, K, bank, topk, pair=pair, rows=sample(M, 12))
