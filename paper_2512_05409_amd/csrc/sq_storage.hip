@@ -7,7 +7,8 @@
 // image of them in LDS: the image starts at the stream's own offset inside 16 bytes, so that whatever the length of a row
 // the stream is read and written 16 bytes at a time, and bit fields of any width and place are ORed into, or cut out of,
 // LDS dwords.  A thread converts 32 channels at a time.  With one thread per byte of the stream, which looked its channel
-// up in the mask, [4096,4096] took 110 us to pack and 33 us to unpack, against 8.7 and 11.1 us.
+// up in the mask, [4096,4096] took 110 us to pack and 33 us to unpack, against 8.7 and 11.1 us.  Short calls are launch and
+// latency only and pack without the image (pack_by_bytes).
 #include "sq_gemm_common.h"
 
 namespace sq {
@@ -15,7 +16,7 @@ namespace {
 
 using gemm::v4u;
 
-constexpr int NT = 256;
+constexpr int kThreads = 256;  // threads of a workgroup (twice as many for long rows)
 
 struct StoreArgs {
   int M, K, B, kt, hh, hl;
@@ -67,7 +68,7 @@ __device__ __forceinline__ int lows_before(const uint32_t* mrow, int w, int wpb)
   return n;
 }
 
-template <bool SENTINEL>
+template <int NT, bool SENTINEL>
 __global__ __launch_bounds__(NT) void pack_storage_kernel(StoreArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint32_t img[];
   const Span s(a);
@@ -133,7 +134,62 @@ __global__ __launch_bounds__(NT) void pack_storage_kernel(StoreArgs a) {
   for (int i = b1 + tid; i < s.end; i += NT) at[i] = static_cast<uint8_t>(img8[i]);
 }
 
+// Channel of the r-th low channel of a bank of mask words (r counts from 0; in range for a malformed mask, too).
+__device__ __forceinline__ int low_channel(const uint32_t* mbank, int wpb, int r) {
+  for (int w = 0; w < wpb; ++w) {
+    uint32_t z = ~mbank[w];
+    const int c = __popc(z);
+    if (r < c) {
+      int at = 32 * w;
+#pragma unroll
+      for (int s = 16; s > 0; s >>= 1) {
+        const int n = __popc(z & ((1u << s) - 1u));
+        if (r >= n) {
+          r -= n;
+          z >>= s;
+          at += s;
+        }
+      }
+      return at;
+    }
+    r -= c;
+  }
+  return 0;
+}
+
+// Short calls: a thread makes one byte of the stream by itself.
 template <bool SENTINEL>
+__global__ __launch_bounds__(kThreads) void pack_bytes_kernel(StoreArgs a) {
+  const unsigned idx = blockIdx.x * kThreads + threadIdx.x;
+  if (idx >= static_cast<unsigned>(a.M) * a.row_bytes) return;
+  const int m = idx / a.row_bytes, b = idx - m * a.row_bytes;
+  uint32_t out = 0;
+  if (b < a.hi_bytes) {
+    const uint8_t* h = reinterpret_cast<const uint8_t*>(a.hi_val) + m * a.K_hi;
+    out = a.hh == 8 ? h[b] : (h[2 * b] & 0xFu) | (h[2 * b + 1] & 0xFu) << 4;
+  } else {
+    const uint32_t* mrow = a.mask + m * a.mask_stride;
+    const uint8_t* drow = a.d_lo + m * (a.K / 2);
+    const int bit0 = 8 * (b - a.hi_bytes), nlo = a.B - a.kt, codes = SENTINEL ? a.K : a.K - a.K_hi;
+    const uint32_t cmask = (1u << a.hl) - 1u;
+    for (int t = bit0 / a.hl; t * a.hl < bit0 + 8 && t < codes; ++t) {
+      int ch = t;
+      bool hi = false;
+      if constexpr (SENTINEL) {
+        hi = (mrow[t >> 5] >> (t & 31)) & 1u;
+      } else {
+        const int bank = t / nlo;
+        ch = bank * a.B + low_channel(mrow + bank * (a.B / 32), a.B / 32, t - bank * nlo);
+      }
+      const uint32_t code = hi ? 1u << (a.hl - 1) : (static_cast<uint32_t>(drow[ch >> 1]) >> (4 * (ch & 1))) & cmask;
+      const int sh = t * a.hl - bit0;
+      out |= sh >= 0 ? code << sh : code >> -sh;
+    }
+  }
+  a.packed[idx] = static_cast<uint8_t>(out);
+}
+
+template <int NT, bool SENTINEL>
 __global__ __launch_bounds__(NT) void unpack_storage_kernel(StoreArgs a) {
   extern __shared__ __attribute__((aligned(16))) uint32_t img[];
   const Span s(a);
@@ -203,6 +259,18 @@ __global__ __launch_bounds__(NT) void unpack_storage_kernel(StoreArgs a) {
   }
 }
 
+// Which calls pack byte by byte.  The image costs two barriers and its atomics, 0.5 to 2 us more than a short call takes
+// without it, but moves 16 bytes per thread; a byte of the sentinel form needs no search, one of the explicit form looks its
+// channel up in the mask words, which costs least where half of them are low, and does not pay for banks of 128 or for more
+// than two codes a byte.  Byte by byte against the image: sentinel [8,512] 2.1 and 2.6 us, k = 32 of 64 [32,11008] 3.0 and
+// 4.8, [128,4096] 3.5 and 3.5, [512,4096] 8.0 and 3.8; explicit k = 32 of 64 [32,4096] 2.9 and 4.0, [512,2048] 5.6 and 3.9,
+// k = 8 of 64 [32,4096] 3.1 and 3.4, [512,1024] 4.5 and 3.4, k = 32 of 128 [32,4096] 4.0 and 3.7.
+bool pack_by_bytes(const sq_params& p, int hl, bool sentinel) {
+  const int64_t n = static_cast<int64_t>(p.M) * p.K;
+  if (sentinel) return n <= (hl == 4 || p.K > 8192 ? 1 << 19 : 1 << 18);
+  return hl == 4 && p.bank <= 64 && n <= (2 * p.topk == p.bank ? 1 << 19 : 1 << 17);
+}
+
 }  // namespace
 
 int launch_storage(const sq_params& p, const sq_act& act, uint8_t* packed, bool pack, bool sentinel, hipStream_t st) {
@@ -222,15 +290,32 @@ int launch_storage(const sq_params& p, const sq_act& act, uint8_t* packed, bool 
   a.d_lo = act.d_lo;
   a.hi_val = act.hi_val;
   a.packed = packed;
-  // enough rows for every thread to have 32 channels: rows of 8192 channels and more go one by one.  The longest row is
-  // 48 KB (65536 channels), below the default limit of dynamic LDS
-  a.rows = p.K >= 32 * NT ? 1 : (32 * NT + p.K - 1) / p.K;
+  if (pack && pack_by_bytes(p, a.hl, sentinel)) {
+    const dim3 grid((p.M * a.row_bytes + kThreads - 1) / kThreads);
+    if (sentinel) hipLaunchKernelGGL(pack_bytes_kernel<true>, grid, dim3(kThreads), 0, st, a);
+    else hipLaunchKernelGGL(pack_bytes_kernel<false>, grid, dim3(kThreads), 0, st, a);
+    return hipGetLastError() == hipSuccess ? SQ_OK : SQ_ERR_LAUNCH;
+  }
+  // Enough rows for every thread to have 32 channels: rows of 8192 channels and more go one by one.  The longest row is
+  // 48 KB (65536 channels), below the default limit of dynamic LDS.  Where that leaves half of the compute units without work,
+  // packing takes half as many rows at a time (sentinel [1016,320] 4.5 -> 3.3 us).
+  constexpr int kChannels = 32 * kThreads;
+  const int cus = device_compute_units();
+  a.rows = (kChannels + p.K - 1) / p.K;
+  if (pack && (p.M + a.rows - 1) / a.rows <= cus / 2) a.rows = (kChannels / 2 + p.K - 1) / p.K;
   const size_t lds = static_cast<size_t>(a.rows) * a.row_bytes + 48;  // the offset in front, and what a 64-bit read passes
   const dim3 grid(static_cast<unsigned>((static_cast<int64_t>(p.M) + a.rows - 1) / a.rows));
-  if (pack && sentinel) hipLaunchKernelGGL(pack_storage_kernel<true>, grid, dim3(NT), lds, st, a);
-  else if (pack) hipLaunchKernelGGL(pack_storage_kernel<false>, grid, dim3(NT), lds, st, a);
-  else if (sentinel) hipLaunchKernelGGL(unpack_storage_kernel<true>, grid, dim3(NT), lds, st, a);
-  else hipLaunchKernelGGL(unpack_storage_kernel<false>, grid, dim3(NT), lds, st, a);
+  // Longer rows take twice the threads ([64,16384] packs in 3.9 us instead of 5.1, unpacks in 4.2 instead of 5.4); packing many
+  // of them does not ([4096,11008] 22.4 instead of 21.6 us).
+  const bool wide = p.K > kChannels && (!pack || p.M <= 2 * cus);
+#define SQ_LAUNCH(KERNEL, SENTINEL)                                                                                      \
+  if (wide) hipLaunchKernelGGL((KERNEL<2 * kThreads, SENTINEL>), grid, dim3(2 * kThreads), lds, st, a);                 \
+  else hipLaunchKernelGGL((KERNEL<kThreads, SENTINEL>), grid, dim3(kThreads), lds, st, a)
+  if (pack && sentinel) { SQ_LAUNCH(pack_storage_kernel, true); }
+  else if (pack) { SQ_LAUNCH(pack_storage_kernel, false); }
+  else if (sentinel) { SQ_LAUNCH(unpack_storage_kernel, true); }
+  else { SQ_LAUNCH(unpack_storage_kernel, false); }
+#undef SQ_LAUNCH
   return hipGetLastError() == hipSuccess ? SQ_OK : SQ_ERR_LAUNCH;
 }
 

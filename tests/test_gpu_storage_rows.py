@@ -1,5 +1,6 @@
 """The storage conversions over whole rows: several rows per workgroup with a last group that is not full, one long row per
-workgroup, streams at every kind of byte offset, against the oracle's streams and back."""
+workgroup, streams at every kind of byte offset, against the oracle's streams and back; and the calls on either side of the
+size from which packing goes through the image of whole rows."""
 import numpy as np
 import pytest
 import torch
@@ -56,3 +57,14 @@ def test_storage_rows(M, K, bank, topk, h_high, h_low, form, offset):
     assert torch.equal(back.d_lo, act.d_lo) and torch.equal(back.hi_val, act.hi_val)
     if sentinel:
         assert torch.equal(back.mask, act.mask)
+
+
+# the last call that packs byte by byte and the first that packs whole rows (every form and rule: sentinel 2^19 channels, 2^18
+# with short codes; explicit 2^17, 2^19 where half of the channels are high; banks of 128 and short codes always whole rows)
+@pytest.mark.parametrize("form,h_high,h_low,K,bank,topk,M", [
+    ("sentinel", 8, 4, 4096, 64, 8, 128), ("sentinel", 4, 2, 1024, 32, 4, 256), ("sentinel", 8, 3, 11008, 64, 8, 47),
+    ("dynamic", 8, 4, 512, 64, 8, 256), ("dynamic", 8, 4, 8192, 64, 32, 64), ("dynamic", 8, 4, 576, 64, 4, 227),
+    ("static", 8, 4, 1024, 32, 16, 512), ("dynamic", 8, 4, 1024, 128, 32, 3), ("dynamic", 8, 3, 1024, 64, 8, 3)])
+def test_ways_of_packing(form, h_high, h_low, K, bank, topk, M):
+    for m in (M, M + 1):
+        test_storage_rows(m, K, bank, topk, h_high, h_low, form, 5)
