@@ -295,17 +295,22 @@ __global__ __launch_bounds__(256) void wsq_gemm_kernel(WsqGemmArgs g) {
 // four tiles' integer registers live, two waves per SIMD) the two hardly overlapped:
 // [4096,4096] x [22016,4096] 1317 -> 1187 us with banks of 64, 1079 -> 888 us with banks of 128; [300,4096] x [4096,4096]
 // 96 -> 66 us; [8,4096] x [12288,4096] 106 -> 66 us (the single-buffered kernel ran there).
-template <int BPB_, int MW_>
+// PAIR (banks of 128): the 128-token tile with the bank's scales read from memory by the lanes, before they copy the next bank
+// (a later read would wait for the copies).  The 2 KB of LDS that this saves let two workgroups share a compute unit: with one,
+// nothing ran under a workgroup's start and epilogue, and shapes of several rounds had become up to 15 % slower than with the
+// 64 x 64 waves ([2566,640] x [9054,640] 92 -> 106 us, now 84 us).
+template <int BPB_, int MW_, bool PAIR = false>
 struct W2 {
   static constexpr int BPB = BPB_, MW = MW_;
   static constexpr int BM = 32 * MW, THREADS = 128 * MW;
   static constexpr int A = 0, WH = BM * 64, WL = WH + 8192, STAGE = WL + 4096;  // a 64-channel stage
-  static constexpr int SC = BPB * STAGE, BANK = SC + 1024;                      // the bank's scales: 128 low, 128 high
+  static constexpr bool SC_LDS = !PAIR;
+  static constexpr int SC = BPB * STAGE, BANK = SC + (SC_LDS ? 1024 : 0);      // the bank's scales: 128 low, 128 high
   static constexpr int FIT = (MW == 4 ? 80 : 160) * 1024 / BANK;  // two workgroups per compute unit, or one
   static constexpr int R = FIT > 4 ? 4 : (FIT < 2 ? 2 : FIT);
   static constexpr int EPI = 2 * MW * 32 * (64 * 4 + 16);  // the epilogue's buffers
   static constexpr int LDS_BYTES = R * BANK > EPI ? R * BANK : EPI;
-  static_assert(LDS_BYTES <= 160 * 1024, "LDS");
+  static_assert(LDS_BYTES <= (PAIR ? 80 : 160) * 1024, "LDS");
 };
 
 __device__ __forceinline__ int w2_off2(int row, int c) { return (row << 5) + (((c ^ (row >> 3)) & 1) << 4); }  // 32-byte rows
@@ -383,7 +388,7 @@ __global__ __launch_bounds__(C::THREADS, 4) void wsq_gemm2_kernel(Wsq2Args g) {
   // per-lane sources of the copies of one stage (at k = 0).  Every wave copies its share of the activations; the weights
   // and the scales are dealt to some of them.
   constexpr int WL0 = MW == 4 ? 0 : 8, WSC = WL0 + 4;  // first wave of the low weights (four of them), wave of the scales
-  const bool has_wh = wave < 8, has_wl = wave >= WL0 && wave < WL0 + 4, has_sc = wave == WSC;
+  const bool has_wh = MW == 4 || wave < 8, has_wl = wave >= WL0 && wave < WL0 + 4, has_sc = C::SC_LDS && wave == WSC;
   const char *pa, *pwh, *pwl, *psc;
   {
     const int row = tid >> 2, c = ((tid & 3) ^ (row >> 2)) & 3;
@@ -429,6 +434,15 @@ __global__ __launch_bounds__(C::THREADS, 4) void wsq_gemm2_kernel(Wsq2Args g) {
     else if (per_bank == 2) w2_wait<(C::R - 2) * 2>();
     else w2_wait<C::R - 2>();
     // the stages of bank - 1 are free: every wave has read them for the last time before this barrier
+    float sl[2], sh[2];
+    if constexpr (!C::SC_LDS) {  // before the copies of the next bank, which the wait for them then leaves in flight
+      const int64_t o = static_cast<int64_t>(bank) * g.Npad + n0 + 64 * wn + r;
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        sl[j] = g.s_lo_t[o + 32 * j];
+        sh[j] = g.s_hi_t[o + 32 * j];
+      }
+    }
     if (bank + C::R - 1 < g.G) issue(bank + C::R - 1);
     const char* st0 = lds + (bank % C::R) * C::BANK;
     const float* sc = reinterpret_cast<const float*>(st0 + C::SC) + 64 * wn + r;
@@ -441,7 +455,10 @@ __global__ __launch_bounds__(C::THREADS, 4) void wsq_gemm2_kernel(Wsq2Args g) {
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       v16i acc_lo = zero, acc_hi = zero;
-      const float sl = sc[32 * j], sh = sc[128 + 32 * j];
+      if constexpr (C::SC_LDS) {
+        sl[j] = sc[32 * j];
+        sh[j] = sc[128 + 32 * j];
+      }
 #pragma unroll
       for (int b = 0; b < BPB; ++b) {
         const char* st = st0 + b * C::STAGE;
@@ -457,8 +474,8 @@ __global__ __launch_bounds__(C::THREADS, 4) void wsq_gemm2_kernel(Wsq2Args g) {
       for (int q = 0; q < 16; ++q) {
         // the widened low weights carry a factor 16, which the transposed low scales carry inverted (sl is
         // s_lo / 16: float(16 a) * (s / 16) is float(a) * s bit for bit while s / 16 is a normal number)
-        float t = __fmul_rn(static_cast<float>(acc_lo[q]), sl);
-        t = __fmaf_rn(static_cast<float>(acc_hi[q]), sh, t);
+        float t = __fmul_rn(static_cast<float>(acc_lo[q]), sl[j]);
+        t = __fmaf_rn(static_cast<float>(acc_hi[q]), sh[j], t);
         f[j][q] = __fadd_rn(f[j][q], t);
       }
     }
@@ -485,11 +502,11 @@ __global__ __launch_bounds__(256) void wsq_scales_t_kernel(int N, int G, int Npa
 
 int init_wsq_kernels() {
   hipError_t e = hipSuccess;
-#define X(BPB, MW)                                                                                       \
+#define X(...)                                                                                           \
   if (e == hipSuccess)                                                                                   \
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(wsq_gemm2_kernel<W2<BPB, MW>>),                \
-                            hipFuncAttributeMaxDynamicSharedMemorySize, W2<BPB, MW>::LDS_BYTES);
-  X(1, 4) X(1, 8) X(2, 4) X(2, 8)
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(wsq_gemm2_kernel<W2<__VA_ARGS__>>),            \
+                            hipFuncAttributeMaxDynamicSharedMemorySize, W2<__VA_ARGS__>::LDS_BYTES);
+  X(1, 4) X(1, 8) X(2, 4) X(2, 8) X(2, 4, true)
 #undef X
   return e == hipSuccess ? SQ_OK : SQ_ERR_LAUNCH;
 }
@@ -558,19 +575,26 @@ int launch_wsq_gemm(const sq_params& p, const int8_t* a8, const float* a_scale, 
     a.y = y;
     a.ldy = ldy;
     a.out_bf16 = p.out_dtype == SQ_OUT_BF16;
-    // 256 tokens per workgroup (30 % less operand traffic) or 128, by the rounds that the 256 compute units make.  A tile
-    // of 256 tokens takes a compute unit alone.  Banks of 64: two of the 128-token tiles share one, do the same work in
-    // about 1.02 of the time and leave no half-empty last round, so the tall tile is taken where its rounds are 15/16
-    // full: 1207 against 1223 us at [4096,4096] x [22016,4096] (2752 tall tiles), but 103 against 59 us and so 128 tokens
-    // at [600,2048] x [11008,2048] (258 tall tiles).  Banks of 128: the LDS holds one workgroup of either form, and a tall
-    // round takes 1.57 short ones, less where the last is light: the tall tile up to two of its rounds for three short
-    // ones.  871 against 1123 us at [4096,4096] x [22016,4096], 42 against 53 us at [1024,2048] x [5120,2048] (one round
-    // for two), but 147 against 112 us and so 128 tokens at [1100,4096] x [6912,4096] (two rounds in either form).
-    const int64_t cols = (p.N + 127) / 128, short_tiles = cols * ((p.M + 127) / 128);
-    const int64_t tall_rounds = (cols * ((p.M + 255) / 256) + 255) / 256;
-    const bool tall = p.bank == 64 ? 480 * tall_rounds <= short_tiles : 3 * tall_rounds <= 2 * ((short_tiles + 255) / 256);
-    if (p.bank == 64) tall ? launch_wsq2<W2<1, 8>>(a, st) : launch_wsq2<W2<1, 4>>(a, st);
-    else tall ? launch_wsq2<W2<2, 8>>(a, st) : launch_wsq2<W2<2, 4>>(a, st);
+    // 256 tokens per workgroup (30 % less operand traffic; it takes a compute unit alone) or 128, by the rounds that the 256
+    // compute units make.  Banks of 64: two of the 128-token tiles share a unit, do the same work in about 1.02 of the time
+    // and leave no half-empty last round, so the tall tile is taken where its rounds are 15/16 full: 1207 against 1223 us at
+    // [4096,4096] x [22016,4096] (2752 tall tiles), but 103 against 59 us and so 128 tokens at [600,2048] x [11008,2048] (258
+    // tall tiles).  Banks of 128: up to one round of 128-token tiles the scales come through LDS (111 against 135 us at
+    // [656,9344] x [369,9344] with the lanes reading them); beyond that pairs of them share a unit (126 against 147 us at
+    // [1505,768] x [23028,768], 88 against 101 us at [1100,4096] x [6912,4096]), unless the tall tiles make one round (178 us
+    // against 196 us for pairs at [493,9472] x [13810,9472]) or 7/8 full ones of long rows (172 against 179 us at [4096,4096] x
+    // [4096,4096]; 554 against 539 us at [4009,1408] x [28591,1408], 315 against 348 us where the last is half empty, at
+    // [1610,5632] x [12399,5632]).
+    const int64_t cols = (p.N + 127) / 128, short_tiles = cols * ((p.M + 127) / 128), tall_tiles = cols * ((p.M + 255) / 256);
+    const int64_t tall_rounds = (tall_tiles + 255) / 256;
+    if (p.bank == 64) {
+      480 * tall_rounds <= short_tiles ? launch_wsq2<W2<1, 8>>(a, st) : launch_wsq2<W2<1, 4>>(a, st);
+    } else if (short_tiles <= 256) {
+      launch_wsq2<W2<2, 4>>(a, st);
+    } else {
+      const bool tall = tall_rounds == 1 ? p.K >= 640 : p.K >= 2048 && 448 * tall_rounds <= short_tiles;
+      tall ? launch_wsq2<W2<2, 8>>(a, st) : launch_wsq2<W2<2, 4, true>>(a, st);
+    }
     return hipGetLastError() == hipSuccess ? SQ_OK : SQ_ERR_LAUNCH;
   }
   WsqGemmArgs g;

@@ -13,12 +13,13 @@ from test_gpu_wsq import case, consumer_order
 pytestmark = pytest.mark.gpu
 
 
-# 256-token tiles where they make few or full rounds of 256: 8 x 31 (banks of 64), 8 x 33 and 3 x 52 (banks of 128, three
-# or two rounds of the smaller tile); 9 x 29 are two rounds, hardly begun, and go to the smaller tile
+# banks of 64: 256-token tiles where they make full rounds of 256 (8 x 31); 9 x 29 are two rounds, hardly begun, and go to the
+# smaller tile.  Banks of 128: up to 256 of the smaller tiles, more of them in pairs on a compute unit (one, two and three
+# banks), the 256-token tiles where they are one round of rows of 768 channels or more
 @pytest.mark.parametrize("M,K,N,bank,pad", [(2100, 64, 3700, 64, 0), (2100, 320, 3650, 64, 3), (2048, 128, 4129, 128, 8),
                                             (1999, 384, 4200, 128, 3), (2000, 64, 3900, 64, 0),
-                                            (2041, 320, 3850, 64, 3), (600, 256, 6600, 128, 3), (1, 64, 20, 64, 0),
-                                            (40, 640, 260, 128, 8), (128, 256, 128, 64, 0),
+                                            (2041, 320, 3850, 64, 3), (600, 256, 6600, 128, 3), (513, 768, 6700, 128, 8),
+                                            (1, 64, 20, 64, 0), (40, 640, 260, 128, 8), (128, 256, 128, 64, 0),
                                             (129, 448, 300, 64, 3)])
 @pytest.mark.parametrize("out_dtype", [sq.SQ_OUT_F32, sq.SQ_OUT_BF16])
 def test_weights_sq_tiles(M, K, N, bank, pad, out_dtype):
