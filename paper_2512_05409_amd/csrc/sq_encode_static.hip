@@ -100,6 +100,7 @@ template <int NT, int IT, bool COMPACT, bool DENSE>
 __global__ __launch_bounds__(NT, IT == 3 ? 6 : 1) void encode_static_gather_kernel(GatherArgs a) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
   constexpr int NWAVE = NT / 64;
+  static_assert(NWAVE == 1 || NWAVE % 4 == 0, "the maxima are combined four waves at a time");
   __shared__ __attribute__((aligned(16))) uint32_t part[2][NWAVE];  // row maxima of the waves: high << 16 | low
   const int row_bytes = 2 * a.K;
   uint32_t* out_sh = reinterpret_cast<uint32_t*>(lds + a.bufs * row_bytes);
@@ -134,10 +135,14 @@ __global__ __launch_bounds__(NT, IT == 3 ? 6 : 1) void encode_static_gather_kern
   for (int w = tid; w < a.K_lo / 8 + 4; w += NT) out_sh[w] = 0;
   uint16_t* tab_hi = reinterpret_cast<uint16_t*>(lds + (a.bufs - 1) * row_bytes);  // channels of the high positions, in the last buffer
   for (int w = tid; w < a.K_hi / 2; w += NT) reinterpret_cast<uint32_t*>(tab_hi)[w] = 0;  // (a malformed mask leaves gaps)
-  if (COMPACT && tid < 256) {  // moves the bytes whose bit of tid is clear together; 0x0C selects a zero byte
+  auto moves = [](uint32_t mask8) {  // moves the bytes whose mask bit is clear together; 0x0C selects a zero byte
     uint64_t s = 0x0C0C0C0C0C0C0C0Cull;
     for (int e = 7; e >= 0; --e)
-      if (!((tid >> e) & 1)) s = (s << 8) | static_cast<uint64_t>(e);
+      if (!((mask8 >> e) & 1)) s = (s << 8) | static_cast<uint64_t>(e);
+    return s;
+  };
+  if (COMPACT && NT >= 256 && tid < 256) {
+    const uint64_t s = moves(tid);
     lut[2 * tid] = static_cast<uint32_t>(s);
     lut[2 * tid + 1] = static_cast<uint32_t>(s >> 32);
   }
@@ -159,9 +164,13 @@ __global__ __launch_bounds__(NT, IT == 3 ? 6 : 1) void encode_static_gather_kern
       mb[i] = (word >> (ch & 31)) & 0xFFu;
       // (a malformed mask: positions past the bank's end stay inside the row and its spare dwords)
       at[i] = static_cast<uint32_t>(bank * nlo + min((ch & (a.B - 1)) - hi, nlo));
-      if (COMPACT) {
+      if (COMPACT && NT >= 256) {
         sel[i][0] = lut[2 * mb[i]];
         sel[i][1] = lut[2 * mb[i] + 1];
+      } else if (COMPACT) {
+        const uint64_t s = moves(mb[i]);
+        sel[i][0] = static_cast<uint32_t>(s);
+        sel[i][1] = static_cast<uint32_t>(s >> 32);
       }
 #pragma unroll
       for (int q = 0; q < 4; ++q)
@@ -228,10 +237,10 @@ __global__ __launch_bounds__(NT, IT == 3 ? 6 : 1) void encode_static_gather_kern
     uint32_t mx = (umax(mx_hi & 0xFFFFu, mx_hi >> 16) << 16) | umax(mx_lo & 0xFFFFu, mx_lo >> 16);
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) mx = pk_max_u16(mx, static_cast<uint32_t>(__shfl_xor(static_cast<int>(mx), off, 64)));
-    if (lane == 0) part[it & 1][wave] = mx;
+    if (NWAVE > 1 && lane == 0) part[it & 1][wave] = mx;
     lds_barrier();  // barrier B: the row has been read for the last time, the waves' maxima are there
     if (m + a.bufs * stride < a.M) stage_row(m + a.bufs * stride, buf);
-    {
+    if constexpr (NWAVE > 1) {
       mx = 0;
 #pragma unroll
       for (int w = 0; w < NWAVE; w += 4) {
@@ -302,9 +311,11 @@ size_t gather_lds_bytes(const sq_params& p, int bufs) {
   return static_cast<size_t>(bufs) * 2 * p.K + K_lo / 2 + 16 + p.K / 8 + 2048;
 }
 
-// Threads and pieces per thread: rows of up to 4096, 8192, 12288, 16384 and 40960 channels.  Eight waves: with four and
-// twice the pieces [4096,4096] took 24.5 us instead of 17 us (the fixed work per wave and row is spread over less).
-#define SQ_STATIC_CFG(X) X(512, 1) X(512, 2) X(512, 3) X(512, 4) X(512, 10)
+// Threads and pieces per thread: rows of up to 512, 1024, 4096, 8192, 12288, 16384 and 40960 channels.  Eight waves: with four
+// and twice the pieces [4096,4096] took 24.5 us instead of 17 us (the fixed work per wave and row is spread over less).  But
+// waves without channels issue as much as the others: rows of up to 1024 channels are a single wave's ([8192,512] 41.5 -> 7.9 us,
+// [8192,64] with b = 32 44 -> 9.5 us, [8,512] 4.8 -> 3.5 us, [8,1024] 4.7 -> 4.4 us).
+#define SQ_STATIC_CFG(X) X(64, 1) X(64, 2) X(512, 1) X(512, 2) X(512, 3) X(512, 4) X(512, 10)
 
 template <int NT, int IT>
 int launch_it(const GatherArgs& a, int blocks, size_t lds, hipStream_t st) {
@@ -362,7 +373,8 @@ int launch_encode_static_gather(const sq_params& p, const uint16_t* x, int64_t l
   a.bufs = gather_lds_bytes(p, 2) <= kLdsLimit ? 2 : 1;
   const size_t lds = gather_lds_bytes(p, a.bufs);
   // as many workgroups as are resident at once, each walking over its share of the rows
-  const int64_t per_cu = static_cast<int64_t>(160 * 1024 / (lds + 64)), most = p.K <= 8192 ? 4 : p.K <= 12288 ? 3 : 2;
+  const int64_t per_cu = static_cast<int64_t>(160 * 1024 / (lds + 64));
+  const int64_t most = p.K <= 1024 ? 16 : p.K <= 8192 ? 4 : p.K <= 12288 ? 3 : 2;
   const int64_t cap = device_compute_units() * (per_cu > most ? most : per_cu);
   const int blocks = static_cast<int>(p.M < cap ? p.M : cap);
 #define X(NT, IT) \

@@ -16,7 +16,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("M,K,bank,topk", [
     (1, 64, 64, 32), (2, 512, 64, 4), (9, 4096, 64, 8), (9, 4160, 64, 32), (5, 8192, 128, 2), (5, 8256, 64, 32),
     (3, 12288, 64, 16), (3, 12352, 64, 32), (3, 16384, 32, 1), (3, 16448, 64, 32), (2, 32768, 64, 8), (2, 34816, 128, 16),
-    (2100, 512, 64, 8), (1700, 8192, 128, 32), (1601, 11008, 64, 16), (600, 34816, 128, 4)])
+    (2100, 512, 64, 8), (5000, 64, 32, 16), (9, 576, 64, 32), (4500, 1024, 128, 16), (7, 1024, 32, 1), (9, 1088, 64, 32), (1700, 8192, 128, 32), (1601, 11008, 64, 16), (600, 34816, 128, 4)])
 @pytest.mark.parametrize("low", ["compact", "dense", "both"])
 def test_static_encoder(M, K, bank, topk, low):
     print(f"static encoder M={M} K={K} bank={bank} topk={topk} low={low}", flush=True)
