@@ -210,8 +210,8 @@ int sq_gemm(const sq_params *p, const sq_act *a, const sq_weight *w, void *y, in
 /* Which of its kernels sq_gemm / sq_linear run for these parameters (static storage, never NULL), by the workgroup's tokens x
  * output channels: "tile256x256" (SQ_DYNAMIC_TIED only), "tile128x256", "tile128x128", "tile64x128", "tile64x64"; the tile
  * is the one whose rounds over the chip take least; or "few_tokens" (up to 32 tokens, up to 64 on layers of at most 8192
- * channels); or "invalid".  Informational: tests use it to state which kernel a case covers.  sq_dense_w4a8_gemm runs what
- * SQ_DYNAMIC_TIED does at its M and N. */
+ * channels); or "tile64x64_light" (short K: several workgroups per compute unit); or "invalid".  Informational: tests use it
+ * to state which kernel a case covers.  sq_dense_w4a8_gemm runs what SQ_DYNAMIC_TIED does at its M, K and N. */
 const char *sq_gemm_variant(const sq_params *p);
 
 /* Which of its kernels sq_encode / sq_linear run for these parameters (static storage, never NULL): dynamic modes

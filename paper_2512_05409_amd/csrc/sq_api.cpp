@@ -118,7 +118,7 @@ int sq_init(void) { return sq::ensure_device_ready(); }
 
 const char* sq_gemm_variant(const sq_params* p) {
   if (check_params(p) != SQ_OK) return "invalid";
-  return sq::gemm_variant_name(p->M, p->N, p->mode == SQ_DYNAMIC_TIED);
+  return sq::gemm_variant_name(p->M, p->N, p->K, p->mode == SQ_DYNAMIC ? 0 : p->mode == SQ_STATIC ? 1 : 2);
 }
 
 const char* sq_encode_variant(const sq_params* p) {

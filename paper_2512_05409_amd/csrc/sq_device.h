@@ -98,10 +98,11 @@ int launch_gemm(const GemmArgs& g, hipStream_t st);
 // Few tokens (sq_gemm_few.hip): which shapes, one-time initialisation, launcher.  mode: 0 dynamic (low + zero-padded
 // high), 1 static (low, then compact high), 2 one INT8 operand.
 bool gemm_few_supports(int M, int N);
+void gemm_few_shape(int M, int N, int* rows, int* ct);  // tokens and 16-channel tiles of a workgroup
 int init_gemm_few_kernels();
 int launch_gemm_few(const GemmArgs& g, int mode, hipStream_t st);
 // Name of the kernel launch_gemm runs for a shape ("tile256x256", "tile128x256", "tile128x128", "tile64x128", "tile64x64",
-// "few_tokens").  single: one product (tied scales, plain W4A8).
-const char* gemm_variant_name(int M, int N, bool single);
+// "tile64x64_light", "few_tokens").  mode: as for launch_gemm_few.
+const char* gemm_variant_name(int M, int N, int K, int mode);
 
 }  // namespace sq

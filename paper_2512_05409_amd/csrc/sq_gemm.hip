@@ -609,34 +609,68 @@ typedef Tile<128, 256, 2, 4> Big;                  // matrix-core bound shapes
 typedef Tile<128, 128, 4, 2> Mid;                  // too few of those to occupy every compute unit
 typedef Tile<64, 128, 2, 2, true, 2> SmallWide;  // fewer still: two K groups of four waves per workgroup, so that a compute
 typedef Tile<64, 64, 2, 2, true, 2> Small;       // unit has two waves per SIMD although it has one workgroup
+typedef Tile<64, 64, 2, 2> Light;                // short K: one K group of four waves, three workgroups per compute unit
 typedef Tile<256, 256, 2, 4, false> Huge;  // single-product modes on large shapes: with one accumulator set a wave
                                            // holds 128 x 64 outputs, which halves the operand traffic and the
                                            // widening arithmetic per matrix instruction
 
-enum Variant { V_HUGE, V_BIG, V_MID, V_SMALL_WIDE, V_SMALL, V_FEW };
+enum Variant { V_HUGE, V_BIG, V_MID, V_SMALL_WIDE, V_SMALL, V_FEW, V_LIGHT };
 
-// Which kernel a shape runs on.  Every tile kernel fills a compute unit with one workgroup, so a launch takes
-// ceil(tiles / 256) rounds, and a round of each tile its own time: at K = 4096, two products, 48 us (Big), 27 us
-// (Mid), 18 us (SmallWide), 11.5 us (Small); single product 35 / 19 / 13.5 / 9 us.  The least rounds x time wins, a
+// Measured times in us, up to 4096 channels, k = channels / 1024; [mode] as in GemmArgs' kernels: two products, static, one
+// product.  A tile that fills a compute unit: launch + rounds * (round + per_k * k).  The light tile: the same with a term for
+// every tile of a compute unit and one for every three.  The few-token kernel: the same with a term for its rows times its
+// channel tiles, over 32 rows.  (Fitted to about 1450 shapes of 1 to 4096 tokens and 64 to 4096 channels, within 10 %.)
+struct TileTime { float launch, round, per_k; };
+struct SharedTime { float launch, each, each_k, group, group_k; };
+constexpr TileTime kBigTime[3] = {{0.16f, 6.29f, 8.00f}, {0.71f, 6.67f, 5.15f}, {0.25f, 5.21f, 4.47f}};
+constexpr TileTime kMidTime[3] = {{1.10f, 4.07f, 5.03f}, {1.45f, 4.57f, 3.47f}, {1.13f, 3.26f, 3.51f}};
+constexpr TileTime kSmallWideTime[3] = {{1.51f, 4.23f, 2.88f}, {1.84f, 4.89f, 2.02f}, {1.53f, 3.49f, 1.99f}};
+constexpr TileTime kSmallTime[3] = {{1.67f, 2.49f, 1.92f}, {1.73f, 3.24f, 1.26f}, {1.70f, 2.17f, 1.36f}};
+constexpr SharedTime kLightTime[3] = {{2.51f, 0.49f, 1.36f, 0.61f, 1.09f}, {3.01f, 0.68f, 0.67f, 0.47f, 1.42f}, {2.29f, 0.29f, 0.88f, 0.93f, 0.98f}};
+constexpr SharedTime kFewTime[3] = {{1.94f, 0.37f, 0.36f, 1.25f, 0.34f}, {2.23f, 0.46f, 0.29f, 1.00f, 0.31f}, {1.94f, 0.32f, 0.26f, 1.07f, 0.31f}};
+
+// Which kernel a shape runs on.  Every tile kernel but the light one fills a compute unit with one workgroup, so a launch takes
+// ceil(tiles / 256) rounds, and a round of each tile its own time: at K = 4096, two products, 46 us (Big), 27 us
+// (Mid), 18 us (SmallWide), 11.5 us (Small); single product 32 / 18.5 / 13.5 / 9 us.  The least rounds x time wins, a
 // larger tile on near ties (it moves less data).  Measured against the old rule (Big above 128 of its tiles, else Mid;
 // 64x64 up to 64 tokens): [333,11008] x [4095,11008] 66.9 -> 42.2 us (SmallWide), [128,4096] x [12288,4096] 26.7 ->
 // 18.2 us, [64,8192] x [28672,8192] 47.5 -> 36.0 us (SmallWide), [512,4096] x [4096,4096] 27.2 -> 19.7 us.
-Variant pick_variant(int M, int N, bool single) {
-  if (gemm_few_supports(M, N)) return V_FEW;
+// With short K a workgroup's start and epilogue count for more than its K steps, and only several workgroups on a compute unit
+// hide them: up to 4096 channels the light tile is taken where the times above say that it is 5 % ahead.  [64,512] x
+// [20000,512] 7.4 us (SmallWide) -> 5.8 us, [32,64] x [28672,64] 6.8 us (few tokens) -> 4.4 us, [512,1024] x [4096,1024] 9.8 ->
+// 8.2 us; but [64,4096] x [12288,4096] 11.7 us (Small) against 14.5 us.
+Variant pick_variant(int M, int N, int K, int mode) {
+  const bool single = mode == 2;
   auto tiles = [&](int bm, int bn) { return static_cast<int64_t>((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
   if (single && tiles(256, 256) >= kHugeMinTiles) return V_HUGE;
-  struct { Variant v; int bm, bn, two, one; } const t[] = {
-      {V_BIG, 128, 256, 460, 320}, {V_MID, 128, 128, 270, 185}, {V_SMALL_WIDE, 64, 128, 180, 135}, {V_SMALL, 64, 64, 115, 90}};
+  const float k = K / 1024.0f;
+  const int64_t each = (tiles(64, 64) + 255) / 256;
+  auto shared = [&](const SharedTime& t, float n, float groups) {
+    return t.launch + n * (t.each + t.each_k * k) + groups * (t.group + t.group_k * k);
+  };
+  const float light = K > 4096 ? 1e30f : shared(kLightTime[mode], each, (each + 2) / 3);
+  if (gemm_few_supports(M, N)) {
+    int rows, ct;
+    gemm_few_shape(M, N, &rows, &ct);
+    const float rounds = ((N + 16 * ct - 1) / (16 * ct) + 255) / 256;
+    return light < 0.95f * shared(kFewTime[mode], rounds * rows * ct / 32.0f, rounds) ? V_LIGHT : V_FEW;
+  }
+  struct { Variant v; int bm, bn, two, one; const TileTime* t; } const t[] = {{V_BIG, 128, 256, 460, 320, kBigTime},
+                                                                              {V_MID, 128, 128, 270, 185, kMidTime},
+                                                                              {V_SMALL_WIDE, 64, 128, 180, 135, kSmallWideTime},
+                                                                              {V_SMALL, 64, 64, 115, 90, kSmallTime}};
   Variant best = V_BIG;
   int64_t least = INT64_MAX;
+  float time = 0.0f;
   for (const auto& c : t) {
-    const int64_t cost = (tiles(c.bm, c.bn) + 255) / 256 * (single ? c.one : c.two);
+    const int64_t rounds = (tiles(c.bm, c.bn) + 255) / 256, cost = rounds * (single ? c.one : c.two);
     if (least == INT64_MAX || cost * 10 < least * 9) {
       least = cost;
       best = c.v;
+      time = c.t[mode].launch + rounds * (c.t[mode].round + c.t[mode].per_k * k);
     }
   }
-  return best;
+  return light < 0.95f * time ? V_LIGHT : best;
 }
 
 template <typename T, int MODE>
@@ -655,6 +689,7 @@ int launch_for_mode(const GemmArgs& g, hipStream_t st, Variant v) {
     case V_BIG: return launch_mode<Big, MODE>(g, st);
     case V_MID: return launch_mode<Mid, MODE>(g, st);
     case V_SMALL_WIDE: return launch_mode<SmallWide, MODE>(g, st);
+    case V_LIGHT: return launch_mode<Light, MODE>(g, st);
     default: return launch_mode<Small, MODE>(g, st);
   }
 }
@@ -669,29 +704,29 @@ int init_gemm_kernels() {
   if (e == hipSuccess) e = raise_lds_limit<T, 0>();          \
   if (e == hipSuccess) e = raise_lds_limit<T, 1>();          \
   if (e == hipSuccess) e = raise_lds_limit<T, 2>();
-  SQ_RAISE(Big) SQ_RAISE(Mid) SQ_RAISE(SmallWide) SQ_RAISE(Small)
+  SQ_RAISE(Big) SQ_RAISE(Mid) SQ_RAISE(SmallWide) SQ_RAISE(Small) SQ_RAISE(Light)
 #undef SQ_RAISE
   if (e == hipSuccess) e = raise_lds_limit<Huge, 2>();
   return e == hipSuccess ? init_gemm_few_kernels() : SQ_ERR_LAUNCH;
 }
 
 // What sq_gemm_variant reports: the choice launch_gemm makes.
-const char* gemm_variant_name(int M, int N, bool single) {
-  switch (pick_variant(M, N, single)) {
+const char* gemm_variant_name(int M, int N, int K, int mode) {
+  switch (pick_variant(M, N, K, mode)) {
     case V_HUGE: return "tile256x256";
     case V_BIG: return "tile128x256";
     case V_MID: return "tile128x128";
     case V_SMALL_WIDE: return "tile64x128";
     case V_SMALL: return "tile64x64";
+    case V_LIGHT: return "tile64x64_light";
     default: return "few_tokens";
   }
 }
 
 int launch_gemm(const GemmArgs& g, hipStream_t st) {
-  const Variant v = pick_variant(g.M, g.N, !g.a_lo);
-  if (g.a_lo && g.a_hi_dense) return launch_for_mode<0>(g, st, v);
-  if (g.a_lo && g.a_hi_compact) return launch_for_mode<1>(g, st, v);
-  if (!g.a_lo && g.a_hi_compact) return launch_for_mode<2>(g, st, v);
+  if (g.a_lo && g.a_hi_dense) return launch_for_mode<0>(g, st, pick_variant(g.M, g.N, g.K, 0));
+  if (g.a_lo && g.a_hi_compact) return launch_for_mode<1>(g, st, pick_variant(g.M, g.N, g.K, 1));
+  if (!g.a_lo && g.a_hi_compact) return launch_for_mode<2>(g, st, pick_variant(g.M, g.N, g.K, 2));
   return SQ_ERR_UNSUPPORTED;
 }
 

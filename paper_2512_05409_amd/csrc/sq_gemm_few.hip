@@ -352,20 +352,25 @@ int init_gemm_few_kernels() {
   return e == hipSuccess ? SQ_OK : SQ_ERR_LAUNCH;
 }
 
-int launch_gemm_few(const GemmArgs& g, int mode, hipStream_t st) {
-  const int mt = g.M <= 8 ? 8 : (g.M + 15) / 16 * 16;
-  const int rows = mt == 16 || mt == 8 || mt > 32 ? mt : 32;  // 17 ... 32 tokens
+void gemm_few_shape(int M, int N, int* rows, int* ct) {
+  const int mt = M <= 8 ? 8 : (M + 15) / 16 * 16;
+  *rows = mt;  // 8, 16, 32, 48 or 64
   // Channels per workgroup: one workgroup fills a compute unit, so the rounds over the chip count, and each costs
   // the workgroup's channels plus about one tile's worth of activations, start and end.
-  int ct = 1, best = 1 << 30;
-  for (int c = 1; c <= (rows > 32 ? 2 : 8); ++c) {
-    const int groups = (g.N + 16 * c - 1) / (16 * c);
+  int best = 1 << 30;
+  for (int c = 1; c <= (mt > 32 ? 2 : 8); ++c) {
+    const int groups = (N + 16 * c - 1) / (16 * c);
     const int cost = (groups + 255) / 256 * (c + 1);
     if (cost <= best) {
       best = cost;
-      ct = c;
+      *ct = c;
     }
   }
+}
+
+int launch_gemm_few(const GemmArgs& g, int mode, hipStream_t st) {
+  int rows, ct;
+  gemm_few_shape(g.M, g.N, &rows, &ct);
   return launch_few_shape(g, mode, rows, ct, st);
 }
 

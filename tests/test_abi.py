@@ -187,12 +187,12 @@ def test_binding_refuses_host_tensors():
 
 def test_gemm_variant_names(L):
     """Which kernel a shape runs on (the GPU tests use this to state what they cover)."""
-    def name(M, N, mode=sq.SQ_DYNAMIC, K=512):
+    def name(M, N, mode=sq.SQ_DYNAMIC, K=8192):
         return sq.sq_gemm_variant(sq.params(M, K, N, mode=mode))
 
     assert name(4096, 22016) == "tile128x256"      # 32 x 86 tiles
-    assert name(1000, 8100) == "tile128x256"       # 8 x 32: one round
-    assert name(1500, 6100) == "tile128x128"       # 12 x 48 tiles, three rounds of 27 against two of 46
+    assert name(1000, 8100) == name(1000, 8100, K=64) == "tile128x256"  # 8 x 32: one round
+    assert name(1500, 6100) == name(500, 8100, K=64) == "tile128x128"   # 12 x 48 tiles, three rounds of 27 against two of 46
     assert name(1300, 6100) == "tile64x128"        # 21 x 48 tiles, four rounds of 18
     assert name(200, 300) == "tile64x64"
     assert name(64, 28672) == "tile64x128"
@@ -202,10 +202,24 @@ def test_gemm_variant_names(L):
     assert name(32, 28672) == name(1, 28672, K=576) == name(8, 28672, mode=sq.SQ_STATIC) == "few_tokens"
     assert name(33, 8193) == "tile64x64" and name(33, 8192) == "few_tokens" and name(65, 64) == "tile64x64"
     assert sq.sq_gemm_variant(sq.params(8, 100, 64)) == "invalid"
-    assert name(4096, 22016, mode=sq.SQ_DYNAMIC_TIED) == "tile256x256"   # 16 x 86 tiles
-    assert name(1000, 8100, mode=sq.SQ_DYNAMIC_TIED) == "tile128x256"
-    assert name(1500, 6100, mode=sq.SQ_DYNAMIC_TIED) == "tile128x128"
-    assert name(8, 28672, mode=sq.SQ_DYNAMIC_TIED) == "few_tokens"
+    tied = sq.SQ_DYNAMIC_TIED
+    assert name(4096, 22016, mode=tied) == "tile256x256"   # 16 x 86 tiles
+    assert name(1000, 8100, mode=tied) == "tile128x256"
+    assert name(1500, 6100, mode=tied) == "tile128x128"
+    assert name(8, 28672, mode=tied) == "few_tokens"
+
+
+def test_short_k_takes_the_light_tile(L):
+    """With short K a workgroup's start and epilogue outweigh its K steps, and only a kernel of which several workgroups share a
+    compute unit hides them: wide layers that the few-token kernel and the tiles of one workgroup per unit run up to a third
+    slower, next to the same shapes with K long enough for those."""
+    def light(M, K, N, mode=sq.SQ_DYNAMIC):
+        return sq.sq_gemm_variant(sq.params(M, K, N, mode=mode)) == "tile64x64_light"
+
+    for mode in (sq.SQ_DYNAMIC, sq.SQ_DYNAMIC_TIED):
+        assert light(32, 64, 28672, mode) and light(64, 512, 20000, mode) and light(48, 512, 28672, mode) and light(512, 512, 4096, mode)
+        assert not light(32, 4096, 28672, mode) and not light(64, 8192, 20000, mode) and not light(512, 8192, 4096, mode)
+        assert not light(8, 512, 4096, mode) and not light(64, 1024, 4096, mode) and not light(4096, 512, 28672, mode)
 
 
 def test_encode_variant_names(L):

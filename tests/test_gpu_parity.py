@@ -147,7 +147,7 @@ def run_gemm(p, enc_host, wq, sw, out_dtype, prepacked=None, static_mask=None):
     return yh, alo.host(np.int32).reshape(M, N), ahi.host(np.int32).reshape(M, N)
 
 
-# small shapes: the 64x64 tile (M > 64) and the few-token kernel with 1 ... 26 K steps shared among its waves, ragged
+# small shapes: the 64x64 tiles (M > 64) and the few-token kernel with 1 ... 26 K steps shared among its waves, ragged
 # M / N / K edges.  The larger tiles need larger shapes: test_gpu_split_k.py, test_gpu_big_tile.py.
 @pytest.mark.parametrize("M,K,N,bank,topk", [(16, 512, 512, 64, 8), (200, 1024, 300, 64, 8), (129, 320, 130, 32, 4),
                                              (64, 2048, 256, 128, 16), (1, 512, 128, 64, 8), (257, 64, 5, 64, 16),

@@ -2,7 +2,7 @@
 
 The shapes are drawn, not hand-picked, so that tile edges, K tails and formats meet combinations nobody thought of; the
 sizes are small enough for the oracle to take a fraction of a second each, and so reach the kernels that small shapes run
-on (the few-token kernel and the 64 x 64 tile)."""
+on (the few-token kernel and the 64 x 64 tiles)."""
 import numpy as np
 import pytest
 import torch

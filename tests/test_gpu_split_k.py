@@ -1,6 +1,7 @@
 """sq_gemm kernels that share K among the waves of a workgroup: the few-token kernel (every token count it has an
 instantiation for, every channel width, K shorter than its waves, partial last steps, both parts of the reordered
-static operands) and the tiles with two K groups (odd and even step counts, a missing and a partial last step).
+static operands) and the tiles with two K groups (odd and even step counts, a missing and a partial last step); and the light
+tile that takes their place where K is short.
 Accumulators and outputs are compared with the oracle bit for bit, into buffers between guard bytes."""
 import numpy as np
 import pytest
@@ -52,13 +53,16 @@ def check(M, K, N, bank, topk, mode):
 @pytest.mark.parametrize("M", [1, 8, 9, 16, 17, 32, 33, 48, 49, 64])
 @pytest.mark.parametrize("mode", [sq.SQ_DYNAMIC, sq.SQ_STATIC, sq.SQ_DYNAMIC_TIED])
 def test_few_tokens_token_counts(M, mode):
+    assert sq.sq_gemm_variant(sq.params(M, 2048, 301, 64, 8, mode=mode)) == "few_tokens"
     check(M, 2048, 301, 64, 8, mode)
 
 
 @pytest.mark.parametrize("N", [4097, 8193, 12300, 16500, 20500, 24600, 28690])
 @pytest.mark.parametrize("M,mode", [(7, sq.SQ_DYNAMIC), (11, sq.SQ_STATIC), (27, sq.SQ_DYNAMIC_TIED), (30, sq.SQ_STATIC)])
 def test_few_tokens_channel_widths(M, N, mode):
-    check(M, 512, N, 64, 8, mode)
+    K = 512 if M <= 16 else 8192  # (short K with more tokens: the light tile)
+    assert sq.sq_gemm_variant(sq.params(M, K, N, 64, 8, mode=mode)) == "few_tokens"
+    check(M, K, N, 64, 8, mode)
 
 
 @pytest.mark.parametrize("K,bank,topk", [(64, 64, 32), (192, 64, 32), (1088, 32, 16), (1152, 128, 32), (5504, 64, 16)])
@@ -67,14 +71,26 @@ def test_few_tokens_channel_tails(M, K, bank, topk, mode):
     check(M, K, 130, bank, topk, mode)
 
 
-TILE_SHAPES = [(65, 64, 70), (130, 128, 515), (100, 192, 260), (333, 1152, 300), (300, 320, 4095), (64, 1024, 8200),
-               (40, 384, 12300), (200, 2048, 8000)]
+TILE_SHAPES = [(65, 1088, 70), (130, 1152, 515), (100, 1216, 260), (333, 1280, 300), (64, 1152, 8200), (40, 1408, 12300),
+               (200, 2112, 8000), (300, 2240, 4095), (130, 2048, 515), (200, 4096, 8000)]
 
 
 @pytest.mark.parametrize("M,K,N,mode", [s + (m,) for s in TILE_SHAPES for m in (sq.SQ_DYNAMIC, sq.SQ_STATIC)]
                          + [s + (sq.SQ_DYNAMIC_TIED,) for s in TILE_SHAPES if s[1] & (s[1] - 1) == 0])
 def test_tiles_with_two_k_groups(M, K, N, mode):
     assert sq.sq_gemm_variant(sq.params(M, K, N, 64, 32, mode=mode)) in ("tile64x64", "tile64x128")
+    check(M, K, N, 64, 32, mode)
+
+
+# the 64 x 64 tile with one K group: one to eight steps, the last one partial or not
+LIGHT_SHAPES = [(65, 64, 70), (130, 128, 515), (100, 192, 260), (40, 384, 12300), (300, 320, 4095), (30, 256, 28690),
+                (64, 512, 20000), (1300, 256, 6100), (500, 960, 4000)]
+
+
+@pytest.mark.parametrize("M,K,N,mode", [s + (m,) for s in LIGHT_SHAPES for m in (sq.SQ_DYNAMIC, sq.SQ_STATIC)]
+                         + [s + (sq.SQ_DYNAMIC_TIED,) for s in LIGHT_SHAPES if s[1] in (256, 512)])
+def test_light_tile(M, K, N, mode):
+    assert sq.sq_gemm_variant(sq.params(M, K, N, 64, 32, mode=mode)) == "tile64x64_light"
     check(M, K, N, 64, 32, mode)
 
 
