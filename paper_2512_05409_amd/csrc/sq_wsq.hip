@@ -576,10 +576,11 @@ int launch_wsq_gemm(const sq_params& p, const int8_t* a8, const float* a_scale, 
     a.ldy = ldy;
     a.out_bf16 = p.out_dtype == SQ_OUT_BF16;
     // 256 tokens per workgroup (30 % less operand traffic; it takes a compute unit alone) or 128, by the rounds that the 256
-    // compute units make.  Banks of 64: two of the 128-token tiles share a unit, do the same work in about 1.02 of the time
-    // and leave no half-empty last round, so the tall tile is taken where its rounds are 15/16 full: 1207 against 1223 us at
-    // [4096,4096] x [22016,4096] (2752 tall tiles), but 103 against 59 us and so 128 tokens at [600,2048] x [11008,2048] (258
-    // tall tiles).  Banks of 128: up to one round of 128-token tiles the scales come through LDS (111 against 135 us at
+    // compute units make.  Banks of 64: two of the 128-token tiles share a unit, so that one's start and epilogue run under the
+    // other's banks: 128 tokens (1106 against 1142 us at [4096,4096] x [22016,4096], 302 against 361 us at [4487,640] x
+    // [21543,640], 59 against 103 us at [600,2048] x [11008,2048]), unless the tall tiles make one round that is 15/16 full
+    // (22.5 against 24.3 us at [398,128] x [16251,128], 101 against 103 us at [716,3456] x [10406,3456]).
+    // Banks of 128: up to one round of 128-token tiles the scales come through LDS (111 against 135 us at
     // [656,9344] x [369,9344] with the lanes reading them); beyond that pairs of them share a unit (126 against 147 us at
     // [1505,768] x [23028,768], 88 against 101 us at [1100,4096] x [6912,4096]), unless the tall tiles make one round (178 us
     // against 196 us for pairs at [493,9472] x [13810,9472]) or 7/8 full ones of long rows (172 against 179 us at [4096,4096] x
@@ -588,7 +589,7 @@ int launch_wsq_gemm(const sq_params& p, const int8_t* a8, const float* a_scale, 
     const int64_t cols = (p.N + 127) / 128, short_tiles = cols * ((p.M + 127) / 128), tall_tiles = cols * ((p.M + 255) / 256);
     const int64_t tall_rounds = (tall_tiles + 255) / 256;
     if (p.bank == 64) {
-      480 * tall_rounds <= short_tiles ? launch_wsq2<W2<1, 8>>(a, st) : launch_wsq2<W2<1, 4>>(a, st);
+      tall_rounds == 1 && short_tiles >= 480 ? launch_wsq2<W2<1, 8>>(a, st) : launch_wsq2<W2<1, 4>>(a, st);
     } else if (short_tiles <= 256) {
       launch_wsq2<W2<2, 4>>(a, st);
     } else {

@@ -13,7 +13,7 @@ from test_gpu_wsq import case, consumer_order
 pytestmark = pytest.mark.gpu
 
 
-# banks of 64: 256-token tiles where they make full rounds of 256 (8 x 31); 9 x 29 are two rounds, hardly begun, and go to the
+# banks of 64: 256-token tiles where they make one full round of 256 (8 x 31); 9 x 29 are two, hardly begun, and go to the
 # smaller tile.  Banks of 128: up to 256 of the smaller tiles, more of them in pairs on a compute unit (one, two and three
 # banks), the 256-token tiles where they are one round of rows of 768 channels or more
 @pytest.mark.parametrize("M,K,N,bank,pad", [(2100, 64, 3700, 64, 0), (2100, 320, 3650, 64, 3), (2048, 128, 4129, 128, 8),
