@@ -636,8 +636,9 @@ constexpr SharedTime kFewTime[3] = {{1.94f, 0.37f, 0.36f, 1.25f, 0.34f}, {2.23f,
 // 64x64 up to 64 tokens): [333,11008] x [4095,11008] 66.9 -> 42.2 us (SmallWide), [128,4096] x [12288,4096] 26.7 ->
 // 18.2 us, [64,8192] x [28672,8192] 47.5 -> 36.0 us (SmallWide), [512,4096] x [4096,4096] 27.2 -> 19.7 us.
 // With short K a workgroup's start and epilogue count for more than its K steps, and only several workgroups on a compute unit
-// hide them: up to 4096 channels the light tile is taken where the times above say that it is 5 % ahead.  [64,512] x
-// [20000,512] 7.4 us (SmallWide) -> 5.8 us, [32,64] x [28672,64] 6.8 us (few tokens) -> 4.4 us, [512,1024] x [4096,1024] 9.8 ->
+// hide them: up to 4096 channels and 1024 tiles the light tile is taken where the times above say that it is 5 % ahead (with
+// more tiles its narrow rows of Y cost more than it gains where they are unaligned or fp32: [2523,128] x [4649,128] 33.8 us
+// against 29.4 us with Mid).  [64,512] x [20000,512] 7.4 us (SmallWide) -> 5.8 us, [32,64] x [28672,64] 6.8 us (few tokens) -> 4.4 us, [512,1024] x [4096,1024] 9.8 ->
 // 8.2 us; but [64,4096] x [12288,4096] 11.7 us (Small) against 14.5 us.
 Variant pick_variant(int M, int N, int K, int mode) {
   const bool single = mode == 2;
@@ -648,7 +649,7 @@ Variant pick_variant(int M, int N, int K, int mode) {
   auto shared = [&](const SharedTime& t, float n, float groups) {
     return t.launch + n * (t.each + t.each_k * k) + groups * (t.group + t.group_k * k);
   };
-  const float light = K > 4096 ? 1e30f : shared(kLightTime[mode], each, (each + 2) / 3);
+  const float light = K > 4096 || each > 4 ? 1e30f : shared(kLightTime[mode], each, (each + 2) / 3);
   if (gemm_few_supports(M, N)) {
     int rows, ct;
     gemm_few_shape(M, N, &rows, &ct);
