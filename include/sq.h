@@ -251,7 +251,8 @@ int sq_linear_noalloc(const sq_params *p, const uint16_t *x_bf16, int64_t ldx, c
  *     f = 0;  for g:  t = fl(float(acc_lo_g) * s_lo[n,g]);  t = fma(float(acc_hi_g), s_hi[n,g], t);  f = fl(f + t)
  *     Y[m,n] = fl(f * s_a[m])
  * `p`: M, K, N, bank (64 or 128), topk (1 ... bank), h_high / h_low (a pair as above), out_dtype; mode is not read.
- * Per-group low scales below 2^-122 are outside the supported range (the compute image stores them divided by 16).
+ * Per-group low scales below 2^-122 are outside the supported range of calls of more than 64 tokens (the compute image
+ * stores them divided by 16).
  * The per-bank scales make the layer bound by vector arithmetic (five instructions per accumulator register and
  * bank), not by the matrix cores.
  */

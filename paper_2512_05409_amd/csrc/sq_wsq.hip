@@ -299,8 +299,11 @@ __global__ __launch_bounds__(256) void wsq_gemm_kernel(WsqGemmArgs g) {
 // (a later read would wait for the copies).  The 2 KB of LDS that this saves let two workgroups share a compute unit: with one,
 // nothing ran under a workgroup's start and epilogue, and shapes of several rounds had become up to 15 % slower than with the
 // 64 x 64 waves ([2566,640] x [9054,640] 92 -> 106 us, now 84 us).
-template <int BPB_, int MW_, bool PAIR = false>
+// TINY: low scales below 2^-122 count, too (see w2_exact).  Calls of up to 64 tokens always took them; keeping the least scale
+// costs them 0.7 %.
+template <int BPB_, int MW_, bool PAIR = false, bool TINY_ = false>
 struct W2 {
+  static constexpr bool TINY = TINY_;
   static constexpr int BPB = BPB_, MW = MW_;
   static constexpr int BM = 32 * MW, THREADS = 128 * MW;
   static constexpr int A = 0, WH = BM * 64, WL = WH + 8192, STAGE = WL + 4096;  // a 64-channel stage
@@ -331,6 +334,7 @@ struct Wsq2Args {
   const int8_t* hi_dense;
   const float* s_lo_t;  // [G, Npad]
   const float* s_hi_t;
+  const float* s_lo;    // [N, G]
   void* y;
   int64_t ldy;
   int out_bf16;
@@ -367,6 +371,40 @@ __device__ __forceinline__ void w2_epilogue(const Wsq2Args& g, char* tb, const f
       } else {
         const OutT* src = reinterpret_cast<const OutT*>(tb + rl * ROW + ch * 16);
         for (int q = 0; q < PER16 && n + q < g.N; ++q) dst[q] = src[q];
+      }
+    }
+  }
+}
+
+// A wave's 32 x 64 sums from the scales as they are given: the transposed low scales are divided by 16, which loses bits of
+// those below 2^-122.  Straight from memory, for the rare tile that has such a scale.
+template <int BPB>
+__device__ __forceinline__ void w2_exact(const Wsq2Args& g, float (&f)[2][16], int m0, int n0, int lane) {
+  const int r = lane & 31, h = lane >> 5;
+  const int8_t* a8 = g.a8 + static_cast<int64_t>(min(m0 + r, g.M - 1)) * g.K;
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int64_t n = min(n0 + 32 * j + r, g.N - 1);
+    const uint8_t* wl = g.lo_clean + n * (g.K / 2);
+    const int8_t* wh = g.hi_dense + n * g.K;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) f[j][q] = 0.0f;
+    for (int bank = 0; bank < g.G; ++bank) {
+      v16i acc_lo = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0}, acc_hi = acc_lo;
+      for (int k = bank * BPB * 64; k < (bank + 1) * BPB * 64; k += 64) {
+        const v4u l = *reinterpret_cast<const v4u*>(wl + k / 2 + 16 * h);
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          const v4i a = *reinterpret_cast<const v4i*>(a8 + k + 16 * (2 * h + s));
+          acc_lo = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, widen_half(l, s), acc_lo, 0, 0, 0);
+          acc_hi = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, *reinterpret_cast<const v4i*>(wh + k + 16 * (2 * h + s)), acc_hi, 0, 0, 0);
+        }
+      }
+      const float sl = g.s_lo[n * g.G + bank], sh = g.s_hi_t[static_cast<int64_t>(bank) * g.Npad + n];
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        const float t = __fmul_rn(static_cast<float>(acc_lo[q] >> 4), sl);
+        f[j][q] = __fadd_rn(f[j][q], __fmaf_rn(static_cast<float>(acc_hi[q]), sh, t));
       }
     }
   }
@@ -426,6 +464,7 @@ __global__ __launch_bounds__(C::THREADS, 4) void wsq_gemm2_kernel(Wsq2Args g) {
 #pragma unroll
     for (int q = 0; q < 16; ++q) f[j][q] = 0.0f;
   const v16i zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+  float least[2] = {1.0f, 1.0f};  // TINY: of the lane's low scales
 
   for (int bank = 0; bank < g.G; ++bank) {
     // this wave's copies of the bank have landed when at most those of the R - 2 banks after it are in flight
@@ -470,6 +509,7 @@ __global__ __launch_bounds__(C::THREADS, 4) void wsq_gemm2_kernel(Wsq2Args g) {
           acc_hi = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[b][s2], wh, acc_hi, 0, 0, 0);
         }
       }
+      if constexpr (C::TINY) least[j] = fminf(least[j], fabsf(sl[j]));
 #pragma unroll
       for (int q = 0; q < 16; ++q) {
         // the widened low weights carry a factor 16, which the transposed low scales carry inverted (sl is
@@ -479,6 +519,11 @@ __global__ __launch_bounds__(C::THREADS, 4) void wsq_gemm2_kernel(Wsq2Args g) {
         f[j][q] = __fadd_rn(f[j][q], t);
       }
     }
+  }
+  if constexpr (C::TINY) {
+    const int n = n0 + 64 * wn + r;  // (beyond N the scales are zero)
+    if (__any((least[0] < 0x1p-126f && n < g.N) || (least[1] < 0x1p-126f && n + 32 < g.N)))
+      w2_exact<BPB>(g, f, m0 + 32 * wm, n0 + 64 * wn, lane);
   }
   __syncthreads();  // the stages are free: y = f * s_a[m]
   char* tb = lds + wave * (32 * (64 * 4 + 16));
@@ -507,6 +552,7 @@ int init_wsq_kernels() {
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(wsq_gemm2_kernel<W2<__VA_ARGS__>>),            \
                             hipFuncAttributeMaxDynamicSharedMemorySize, W2<__VA_ARGS__>::LDS_BYTES);
   X(1, 4) X(1, 8) X(2, 4) X(2, 8) X(2, 4, true)
+  X(1, 4, false, true) X(2, 4, false, true) X(2, 4, true, true)
 #undef X
   return e == hipSuccess ? SQ_OK : SQ_ERR_LAUNCH;
 }
@@ -572,6 +618,7 @@ int launch_wsq_gemm(const sq_params& p, const int8_t* a8, const float* a_scale, 
     a.hi_dense = hi_dense;
     a.s_lo_t = s_lo_t;
     a.s_hi_t = s_hi_t;
+    a.s_lo = w.scale_lo;
     a.y = y;
     a.ldy = ldy;
     a.out_bf16 = p.out_dtype == SQ_OUT_BF16;
@@ -588,7 +635,10 @@ int launch_wsq_gemm(const sq_params& p, const int8_t* a8, const float* a_scale, 
     // [1610,5632] x [12399,5632]).
     const int64_t cols = (p.N + 127) / 128, short_tiles = cols * ((p.M + 127) / 128), tall_tiles = cols * ((p.M + 255) / 256);
     const int64_t tall_rounds = (tall_tiles + 255) / 256;
-    if (p.bank == 64) {
+    if (p.M <= 64) {
+      if (p.bank == 64) launch_wsq2<W2<1, 4, false, true>>(a, st);
+      else short_tiles <= 256 ? launch_wsq2<W2<2, 4, false, true>>(a, st) : launch_wsq2<W2<2, 4, true, true>>(a, st);
+    } else if (p.bank == 64) {
       tall_rounds == 1 && short_tiles >= 480 ? launch_wsq2<W2<1, 8>>(a, st) : launch_wsq2<W2<1, 4>>(a, st);
     } else if (short_tiles <= 256) {
       launch_wsq2<W2<2, 4>>(a, st);

@@ -9,6 +9,7 @@ import oracle.wsq as W
 import paper_2512_05409_amd as sq
 from gpu_util import Guarded, dev
 from test_gpu_wsq import case, consumer_order
+from workloads import pack_int4
 
 pytestmark = pytest.mark.gpu
 
@@ -63,3 +64,42 @@ def test_activation_quantiser_row_lengths(K, bits):
     sa.check()
     assert np.array_equal(a8.host(np.int8).reshape(M, K), consumer_order(codes))
     assert np.array_equal(sa.host(np.uint32), scale.view(np.uint32))
+
+
+@pytest.mark.parametrize("M,K,N,bank", [(1, 64, 70, 64), (64, 320, 300, 64), (33, 128, 129, 128), (50, 384, 260, 128), (2, 256, 33000, 128)])
+@pytest.mark.parametrize("special", ["tiny", "zero"])
+def test_low_scales_below_the_image_s_range(M, K, N, bank, special):
+    """Up to 64 tokens: low scales that the image, which holds them divided by 16, cannot (below 2^-122, down to the smallest
+    subnormal; and zero).  Also in a single channel of a tile, and next to ordinary ones."""
+    print(f"wsq tiny scales M={M} K={K} N={N} bank={bank} {special}", flush=True)
+    rng = np.random.default_rng(M + K + N)
+    G, topk = K // bank, bank // 8
+    lo = rng.integers(-7, 8, size=(N, G, bank)).astype(np.int8)
+    high = np.argsort(rng.random((N, G, bank)), -1)[..., :topk]
+    np.put_along_axis(lo, high, -8, -1)
+    hi_val = rng.integers(-127, 128, size=(N, G, topk)).astype(np.int8)
+    s_lo = rng.uniform(0.01, 0.02, (N, G)).astype(np.float32)
+    s_hi = rng.uniform(0.001, 0.002, (N, G)).astype(np.float32)
+    rows = np.r_[5, 40:48, 64, 69]  # (tiles of 32 channels without one, with one, with several, and the ragged last one)
+    exp = rng.integers(-149, -118, (len(rows), G))
+    s_lo[rows] = 0 if special == "zero" else np.ldexp(rng.uniform(1, 2, (len(rows), G)), exp).astype(np.float32)
+    s_hi[rows] = np.ldexp(rng.uniform(1, 2, (len(rows), G)), exp - 3).astype(np.float32)
+    if special == "tiny":
+        s_lo[rows[0]] = np.float32(2.0 ** -149)
+    codes = rng.integers(-127, 128, size=(M, K)).astype(np.int8)
+    scale = np.full(M, 2.0 ** 100, np.float32)
+    scale[0] = 0.37
+    prod = W.gemm(codes, scale, W.WeightSQ(N, K, bank, topk, 8, 4, lo.reshape(N, K), hi_val, s_lo, s_hi))
+    p = sq.params(M, K, N, bank, topk, out_dtype=sq.SQ_OUT_F32)
+    ws = sq.WeightSQ(p)
+    ws.lo.copy_(dev(pack_int4(lo.reshape(N, K))).view(-1))
+    ws.hi_val.copy_(dev(hi_val).view(-1))
+    ws.scale_lo.copy_(dev(s_lo).view(-1))
+    ws.scale_hi.copy_(dev(s_hi).view(-1))
+    pre = torch.empty(sq.sq_wsq_prepack_bytes(p), dtype=torch.uint8, device="cuda")
+    sq.sq_wsq_prepack(p, ws, pre)
+    y = Guarded(M * N * 4, torch.float32)
+    sq.sq_wsq_gemm(p, dev(consumer_order(codes)), dev(scale), ws, pre, y.t)
+    torch.cuda.synchronize()
+    y.check()
+    assert np.array_equal(y.host(np.uint32).reshape(M, N), prod.y32.view(np.uint32))
