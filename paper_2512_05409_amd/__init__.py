@@ -177,6 +177,15 @@ def _ptr(t) -> Optional[int]:
 _raw_stream = None  # torch's (device) -> stream handle and () -> device, once looked up
 
 
+def _forget_raw_stream() -> None:
+    global _raw_stream
+    _raw_stream = None
+
+
+# A forked child cannot use the parent's device: asked through torch again, it gets torch's error instead of a launch.
+os.register_at_fork(after_in_child=_forget_raw_stream)
+
+
 def _stream(stream) -> Optional[int]:
     """Handle of `stream`, or of the current stream (asked for as a number: a torch.cuda.Stream object, made only to read
     its handle, costs a small call about a tenth of its time)."""

@@ -185,6 +185,17 @@ def test_binding_refuses_host_tensors():
         sq._ptr(torch.zeros(4))
 
 
+def test_stream_handle_is_asked_for_again_after_a_fork(monkeypatch):
+    """torch refuses the device in a child forked after it was initialised; the handle's short cut must not pass that by."""
+    monkeypatch.setattr(sq, "_raw_stream", (lambda device: 0x1234, lambda: 0))
+    assert sq._stream(None) == 0x1234
+    pid = os.fork()
+    if pid == 0:
+        os._exit(7 if sq._raw_stream is None else 1)
+    assert os.waitstatus_to_exitcode(os.waitpid(pid, 0)[1]) == 7
+    assert sq._stream(None) == 0x1234
+
+
 def test_gemm_variant_names(L):
     """Which kernel a shape runs on (the GPU tests use this to state what they cover)."""
     def name(M, N, mode=sq.SQ_DYNAMIC, K=8192):
