@@ -104,7 +104,7 @@ typedef struct {
                        codes of the low channels only, ascending channel order, two per byte -- the activations
                        "selected and gathered" by the mask (Section 3.3), the operand that goes with the reordered
                        weights of sq_weight_prepack.  A pure function of (d_lo, mask).  sq_encode writes it when the
-                       pointer is set (K <= 65535 and K <= about 37000 so that a row fits in LDS; otherwise
+                       pointer is set (K <= about 37000 so that a row fits in LDS; otherwise
                        SQ_ERR_UNSUPPORTED); then d_lo may be NULL.  sq_gemm multiplies it when set (the low
                        product then runs over K_lo channels) and d_lo otherwise (over K). */
 } sq_act;

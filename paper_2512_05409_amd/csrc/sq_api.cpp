@@ -70,7 +70,8 @@ int check_params(const sq_params* p) {
 
 inline int k_hi_of(const sq_params* p) { return (p->K / p->bank) * p->topk; }
 // Static mode with a handful of tokens.  The sizes of the two workspaces of these shapes include an image of the high
-// part that the kernels no longer need (sq_gemm multiplies the compact codes); the sizes stay as callers know them.
+// part that no kernel reads (sq_gemm multiplies the compact codes).  They are results that callers lay their buffers out by and
+// hand back (a smaller buffer is SQ_ERR_WORKSPACE), so they stay as they were; at 32 tokens the image is at most 2 MiB.
 inline bool static_decode(const sq_params* p) { return p->mode == SQ_STATIC && p->M <= 32 && p->K % 128 == 0; }
 inline size_t lo_compact_bytes(const sq_params* p) { return static_cast<size_t>(p->M) * ((p->K - k_hi_of(p)) / 2); }
 

@@ -95,7 +95,8 @@ __device__ __forceinline__ void quant8(const uint32_t* pairs, float inv, uint32_
 
 // LDS: the row buffers [K * 2], the compact row [K_lo / 2 + 16], the mask [K / 8].
 // NT: threads; IT: pieces a thread owns at most (with 3, registers for three workgroups per compute unit, which is what
-// LDS holds of such rows: 34.6 us with three, 35.9 us with two at 11008 channels).  COMPACT / DENSE: lo_compact / d_lo are written.
+// LDS holds of such rows: 34.6 us with three, 35.9 us with two at 11008 channels, although 4 of the 80 registers are spilled
+// then, and 21 where both forms of the low part are written).  COMPACT / DENSE: lo_compact / d_lo are written.
 template <int NT, int IT, bool COMPACT, bool DENSE>
 __global__ __launch_bounds__(NT, IT == 3 ? 6 : 1) void encode_static_gather_kernel(GatherArgs a) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
@@ -116,7 +117,7 @@ __global__ __launch_bounds__(NT, IT == 3 ? 6 : 1) void encode_static_gather_kern
   auto mine = [&](int n) { return (n - wave * 64 + NT - 1) / NT; };
   const int n_copy = mine(chunks), n_store = mine(n_hi) + (COMPACT ? mine(out16) : 0) + (DENSE ? mine(chunks) : 0);
 
-  // thread t copies pieces t, t + 256, ... (1 KB of consecutive memory per wave instruction)
+  // thread t copies pieces t, t + NT, ... (1 KB of consecutive memory per wave instruction)
   auto stage_row = [&](int64_t m, int buf) {
     const char* xrow = reinterpret_cast<const char*>(a.x + m * a.ldx);
     char* row = lds + buf * row_bytes;
@@ -333,9 +334,10 @@ hipError_t raise_static() {
 
 }  // namespace
 
-// Rows up to 65535 channels (16-bit table entries); the bound on the LDS is that of two buffers' worth per channel.
+// Rows of up to about 37000 channels: the bound that callers know, what a row and two tables of 16-bit channel numbers for it
+// would take.  (One row buffer and the compact row take a little less.)
 bool encode_static_gather_supports(const sq_params& p) {
-  if (p.K > 40960) return false;  // pieces per thread; also keeps the table's entries in 16 bits
+  if (p.K > 40960) return false;  // pieces per thread; also keeps the channel numbers in 16 bits
   const size_t row = (static_cast<size_t>(p.K) * 2 + 4095) / 4096 * 4096;
   return row + static_cast<size_t>(p.K) * 2 + p.K / 8 + 64 <= 150 * 1024;
 }

@@ -22,7 +22,7 @@
 // SIMD, a quarter less LDS traffic per matrix instruction) [4096,4096] x [22016,4096] took 575 us against 526 us,
 // [2048,4096] x [12288,4096] 155 against 147 us, the single-product 256 x 256 tile 308 against 275 us.
 // Smaller tiles, of which a shape has at most a round, run two groups of four waves per workgroup, each on every other
-// K step.
+// K step; where K is short, one group of four waves and several workgroups per compute unit (pick_variant).
 // A K step of 128 channels is copied into one of three LDS stages by LDS-direct loads, two steps
 // ahead of its use.  LDS rows are row-major with the 16-byte chunk index XOR-swizzled by the row,
 // which keeps the operand reads (32 consecutive rows per half wave) free of bank conflicts.
@@ -486,8 +486,6 @@ __device__ __forceinline__ void epilogue(const GemmArgs& g, const EpiScales<T>& 
   else epilogue_typed<T, float>(g, es, lds, acc_lo, acc_hi, m0, n0, wm, wn, wave, lane);
 }
 
-// MODE 0: dynamic (low + zero-padded high in one K loop); 1: static (low loop over K, then the
-// compact high loop over K_hi); 2: high loop only (plain W4A8 reference).
 // Adds the K groups' partial sums (integers: exact in any order) into the first group's registers, through LDS.
 // Every stage has been read for the last time (k_loop ends with a barrier); on return LDS is free again.
 template <typename T, bool LO>
@@ -531,6 +529,8 @@ __device__ __forceinline__ void join_groups(char* lds, int grp, int wave, int la
   __syncthreads();  // the epilogue reuses the space
 }
 
+// MODE 0: dynamic (low + zero-padded high in one K loop); 1: static (low loop over K or K_lo, then the compact high loop
+// over K_hi); 2: one INT8 operand (tied scales, plain W4A8).
 template <typename T, int MODE>
 __global__ __launch_bounds__(T::THREADS) void gemm_kernel(GemmArgs g) {
   extern __shared__ __attribute__((aligned(16))) char lds_all[];
