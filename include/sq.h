@@ -50,7 +50,7 @@ typedef enum {
   SQ_ERR_ALIGN = -4,       /* pointer or leading dimension breaks the alignment rule */
   SQ_ERR_LAUNCH = -5,      /* the HIP runtime refused a launch */
   SQ_ERR_MASK = -6,        /* (prepack, host check) a bank of the static mask does not hold exactly topk bits */
-  SQ_ERR_WORKSPACE = -7,   /* workspace NULL or smaller than sq_workspace_bytes() */
+  SQ_ERR_WORKSPACE = -7,   /* workspace NULL or smaller than its query returns */
   SQ_ERR_SCRATCH = -8      /* sq_linear_noalloc: the problem needs more than SQ_NOALLOC_SCRATCH_BYTES of workspace */
 } sq_status;
 

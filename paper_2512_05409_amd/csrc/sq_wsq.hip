@@ -293,8 +293,8 @@ __global__ __launch_bounds__(256) void wsq_gemm_kernel(WsqGemmArgs g) {
 // share a SIMD, and one wave's fold runs under the others' matrix instructions.  That fold bounds the kernel: 1280 cycles
 // per 64 x 64 outputs and bank against 512 * BPB of matrix instructions.  With four waves of 64 x 64 per workgroup (all
 // four tiles' integer registers live, two waves per SIMD) the two hardly overlapped:
-// [4096,4096] x [22016,4096] 1317 -> 1187 us with banks of 64, 1079 -> 888 us with banks of 128; [300,4096] x [4096,4096]
-// 96 -> 66 us; [8,4096] x [12288,4096] 106 -> 66 us (the single-buffered kernel ran there).
+// [4096,4096] x [22016,4096] 1241 -> 1106 us with banks of 64, 1012 -> 868 us with banks of 128 (whole calls, in turn on one
+// card); [300,4096] x [4096,4096] 96 -> 66 us; [8,4096] x [12288,4096] 106 -> 66 us (the single-buffered kernel ran there).
 // PAIR (banks of 128): the 128-token tile with the bank's scales read from memory by the lanes, before they copy the next bank
 // (a later read would wait for the copies).  The 2 KB of LDS that this saves let two workgroups share a compute unit: with one,
 // nothing ran under a workgroup's start and epilogue, and shapes of several rounds had become up to 15 % slower than with the
