@@ -1,6 +1,8 @@
 """Builds libsq.so (the HIP kernels and their C ABI) in-tree for gfx950 with hipcc."""
 from __future__ import annotations
 
+import glob
+import hashlib
 import os
 import subprocess
 import sys
@@ -29,9 +31,19 @@ def _hipcc() -> str:
     raise RuntimeError("hipcc not found")
 
 
-def _compile(src: str) -> str:
+def sources_digest() -> str:
+    """Digest of everything the library is compiled from: the sources, the headers and the flags."""
+    h = hashlib.sha256(" ".join(f for f in HIP_FLAGS if not f.startswith("-I")).encode())
+    files = [os.path.join(CSRC, s) for s in sorted(SOURCES)] + sorted(glob.glob(os.path.join(CSRC, "*.h")))
+    for path in files + [os.path.join(ROOT, "include", "sq.h")]:
+        with open(path, "rb") as f:
+            h.update(os.path.basename(path).encode() + b"\0" + f.read() + b"\0")
+    return h.hexdigest()
+
+
+def _compile(src: str, digest: str) -> str:
     obj = os.path.join(OBJ, os.path.splitext(src)[0] + ".o")
-    cmd = [_hipcc()] + HIP_FLAGS + ["-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj]
+    cmd = [_hipcc()] + HIP_FLAGS + [f'-DSQ_SOURCES="{digest}"', "-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         sys.stderr.write(r.stdout + r.stderr)
@@ -44,8 +56,9 @@ def _compile(src: str) -> str:
 
 def build(verbose: bool = False) -> str:
     os.makedirs(OBJ, exist_ok=True)
+    digest = sources_digest()
     with ThreadPoolExecutor(max_workers=4) as ex:
-        objs = list(ex.map(_compile, SOURCES))
+        objs = list(ex.map(_compile, SOURCES, [digest] * len(SOURCES)))
     cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:

@@ -552,4 +552,10 @@ const char* sq_status_string(int status) {
 
 const char* sq_version(void) { return "0.1"; }
 
+/* What the build compiled the library from (build.py: sources_digest), so that a test can tell a library that was
+ * left over from other sources. */
+#ifdef SQ_SOURCES
+__attribute__((visibility("default"), used)) extern const char sq_sources[65] = SQ_SOURCES;
+#endif
+
 }  // extern "C"

@@ -33,6 +33,21 @@ def test_every_declared_symbol_is_exported(L):
         assert getattr(L, n) is not None
 
 
+def _built_from_these_sources():
+    from paper_2512_05409_amd import build
+    return (ctypes.c_char * 65).in_dll(sq.lib(), "sq_sources").value.decode() == build.sources_digest()
+
+
+def test_library_is_built_from_these_sources(L):
+    """A library left over from other sources would make every other result here say nothing about this tree."""
+    assert _built_from_these_sources(), "libsq.so is stale: build again"
+
+
+@pytest.mark.gpu
+def test_library_under_gpu_test_is_built_from_these_sources(L):
+    assert _built_from_these_sources(), "libsq.so is stale: build again"
+
+
 def test_storage_row_holds_every_bit(L):
     """Every bit of the two sections has a place in the row, also where the low section is not whole bytes."""
     for K in range(64, 1344, 64):
